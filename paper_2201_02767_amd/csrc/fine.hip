@@ -1,8 +1,9 @@
 // Gathered fine attention at the finer levels: one wave per (parent query, head) work item, or per
 // pair of neighbouring parents on maps of one row; the per-item work (its independent loads in
 // item_head, then gather, MFMA logits, softmax, top-K, messages, the finest level's combination in
-// fine_item, both in fine_item.h). A workgroup holds up to four independent waves (fewer when a
+// fine_item, both in fine_item.h; bf16 maps without a fused position encoding: fine_bf16.h). A workgroup holds up to four independent waves (fewer when a
 // wave's LDS region is large: 256 fp32 slots of d = 64); nothing synchronises across waves.
+#include "fine_bf16.h"
 #include "fine_item.h"
 
 namespace qta {
@@ -54,8 +55,54 @@ hipError_t launch_one(const FineArgs& a, hipStream_t stream)
     return hipGetLastError();
 }
 
+// The bf16 form (fine_bf16.h), NT tiles of 16 candidate slots.
+template <int D, int NT, bool VA, bool FINEST, bool ROW>
+__global__ __launch_bounds__(256) void fine_bf16_kernel(FineArgs a)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int wpb = blockDim.x >> 6;
+    const int np = a.Hp * a.Wp;
+    const int nitems = a.B * a.heads * (ROW ? (np + 1) / 2 : np);   // below 2^31 (checked by the launcher)
+    const int it = xcd_remap(blockIdx.x, gridDim.x) * wpb + wave;
+    if (it >= nitems) return;              // whole wave leaves; only wave-level syncs follow
+    extern __shared__ __align__(16) unsigned char smem[];
+    fine16::item<D, NT, VA, FINEST, ROW>(a, it, smem + wave * fine16::wave_bytes<D, NT>());
+}
+
+template <int D, int NT, bool VA, bool FINEST, bool ROW>
+hipError_t launch_bf16(const FineArgs& a, hipStream_t stream)
+{
+    constexpr size_t wave_bytes = fine16::wave_bytes<D, NT>();
+    int wpb = 4;
+    while (wpb > 1 && wpb * wave_bytes > device_max_lds()) --wpb;
+    if (wave_bytes > device_max_lds()) return hipErrorInvalidValue;
+    static std::atomic<unsigned long long> configured{0};     // devices whose LDS limit is raised
+    if (hipError_t e = set_max_lds_once(reinterpret_cast<const void*>(&fine_bf16_kernel<D, NT, VA, FINEST, ROW>), configured);
+        e != hipSuccess)
+        return e;
+    const long long np = static_cast<long long>(a.Hp) * a.Wp;
+    const long long items = static_cast<long long>(a.B) * a.heads * (ROW ? (np + 1) / 2 : np);
+    const long long blocks = (items + wpb - 1) / wpb;
+    if (blocks * wpb >= 0x7FFFFFFFLL) return hipErrorInvalidValue;     // work items are int
+    hipLaunchKernelGGL((fine_bf16_kernel<D, NT, VA, FINEST, ROW>), dim3(static_cast<unsigned>(blocks)),
+                       dim3(wpb * kWave), wpb * wave_bytes, stream, a);
+    return hipGetLastError();
+}
+
+template <int D, bool VA, bool FINEST, bool ROW>
+hipError_t launch_bf16_tiles(const FineArgs& a, hipStream_t stream)
+{
+    const int nslot = 4 * a.Kp;
+    if (nslot <= 16) return launch_bf16<D, 1, VA, FINEST, ROW>(a, stream);
+    if (nslot <= 32) return launch_bf16<D, 2, VA, FINEST, ROW>(a, stream);
+    if (nslot <= 64) return launch_bf16<D, 4, VA, FINEST, ROW>(a, stream);
+    if (nslot <= 128) return launch_bf16<D, 8, VA, FINEST, ROW>(a, stream);
+    if (nslot <= 256) return launch_bf16<D, 16, VA, FINEST, ROW>(a, stream);
+    return hipErrorInvalidValue;
+}
+
 template <typename T, int D, bool VA, bool FINEST, bool ROW, bool PE>
-hipError_t launch_nsp_pe(const FineArgs& a, hipStream_t stream)
+hipError_t launch_general(const FineArgs& a, hipStream_t stream)
 {
     const int nslot = 4 * a.Kp;
     if (nslot <= 16) return launch_one<T, D, 16, VA, FINEST, ROW, PE>(a, stream);
@@ -66,6 +113,15 @@ hipError_t launch_nsp_pe(const FineArgs& a, hipStream_t stream)
         if (nslot <= 256) return launch_one<T, D, 256, VA, FINEST, ROW, PE>(a, stream);
     }
     return hipErrorInvalidValue;
+}
+
+template <typename T, int D, bool VA, bool FINEST, bool ROW, bool PE>
+hipError_t launch_nsp_pe(const FineArgs& a, hipStream_t stream)
+{
+    // (measured on the layers of the workloads: the bf16 form 14-25% faster than the general one; it has no
+    // fused encoding, whose per-lane kernels cost it what the rest gains)
+    if constexpr (sizeof(T) == 2 && !PE) return launch_bf16_tiles<D, VA, FINEST, ROW>(a, stream);
+    else return launch_general<T, D, VA, FINEST, ROW, PE>(a, stream);
 }
 
 // Levels of maps with more than one row may fuse their position encoding (a.pe_w).
@@ -104,6 +160,8 @@ hipError_t launch_fine_attn(const FineArgs& a, int d, bool variant_a, bool bf16_
     if (finest && (a.q_blocked || a.kv_blocked)) return hipErrorInvalidValue;   // level 0 is NHWC
     FineArgs b = a;
     b.inv_levels = a.levels > 0 ? 1.0f / static_cast<float>(a.levels) : 0.f;
+    for (int l = 1; l < a.levels; ++l)
+        b.anc[l] = FineArgs::Ancestors{a.coarser_msg[l], a.lvl_W[l], static_cast<uint32_t>(a.lvl_N[l]) * static_cast<uint32_t>(a.C)};
     b.div_Wp = make_fastdiv(a.Wp);
     b.div_heads = make_fastdiv(a.heads);
     const int np = a.Hp * a.Wp;

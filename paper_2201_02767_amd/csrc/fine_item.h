@@ -1,6 +1,7 @@
 // The per-item body of the gathered fine attention (steps 3-5 at the finer levels; Sec. 3.2,
 // Fig. 1; QuadTree-A scores Eq. 4, QuadTree-B softmax Eq. 6; the finest level's combination,
-// Eqs. 2 and 5), included by the fine kernels of every finer level.
+// Eqs. 2 and 5): the form for fp32 maps, and for bf16 maps with a fused position encoding. bf16 maps
+// without one take fine_bf16.h.
 //
 // Work item = one parent query P at level l+1 and one head. Its four children at level l are
 // sibling queries with one shared candidate set: the 2x2 children of the K keys P kept (4K <= 256
@@ -42,7 +43,6 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 constexpr int kMaxSlots = 256;         // candidate slots of one item: 4 K_l for K_l <= 64, up to four per lane
 constexpr int kMaxSlotsPe = 64;        // with a fused position encoding: one slot per lane
-constexpr int kSplitSlots = 64;        // bf16 value rows staged at a time when a group has 65 .. 128 slots
 constexpr int kPrefetchLevels = 4;    // the finest level prefetches up to this many ancestors
 // LDS pitch (elements) of one channel's 16 tokens in the fused position encoding: 20 puts the four lane
 // groups' writes and neighbouring channels' row reads in different banks (16 would stack them)
@@ -63,9 +63,7 @@ __host__ __device__ inline WaveLds wave_lds(int nsp)
     L.v = 0;
     int vbytes;
     if (TB == 2) {
-        // Vt[channel][slot]; with 65 .. 128 slots the rows are staged in two halves of at most 64
-        // slots (half the LDS per wave, so that registers rather than LDS bound the occupancy)
-        L.vpitch = (nsp > kSplitSlots && nsp <= 2 * kSplitSlots ? kSplitSlots : nsp) + 8;
+        L.vpitch = nsp + 8;                 // Vt[channel][slot]
         vbytes = D * L.vpitch * 2;
     } else {
         L.vpitch = D + 4;                   // Vs[slot][channel]
@@ -190,10 +188,7 @@ __device__ __forceinline__ void fine_item(const FineArgs& a, const ItemHead<T, D
     constexpr int NH = 16 / NCG;           // PV: slot halves (2 for d = 32, 1 for d = 64)
     constexpr int QPL = 4 / NH;            // output queries per lane
     constexpr int SPL = NSP > 64 ? NSP / 64 : 1;   // candidate slots per lane: lane + 64u
-    // bf16 with 65 .. 128 slots: slots 0 .. 63 are staged as their tiles are consumed, the value rows
-    // of slots 64 .. are held in registers and staged after the first half of the messages
-    constexpr bool kSplitV = kBf16 && NSP == 2 * kSplitSlots;
-    constexpr int kTS = kSplitSlots / 16;           // tiles of the first half
+    static_assert(!kBf16 || PE, "bf16 maps without a fused position encoding take fine_bf16.h");
     static_assert(!PE || !ROW, "the fused position encoding is for maps of more than one row");
     static_assert(NSP <= kMaxSlotsPe || !PE, "a fused position encoding takes at most 64 slots");
 
@@ -241,8 +236,8 @@ __device__ __forceinline__ void fine_item(const FineArgs& a, const ItemHead<T, D
     //      the gathers, needs the kept keys ----
     // With more tiles than one batch of registers holds, a compiler barrier: the kept keys of the
     // later batches (gathered behind a uniform bound) would otherwise be sunk to those batches,
-    // leaving each a dependent load chain of its own (detection's 128-slot finest level +1.6 us).
-    // With a single batch the barrier only constrains the schedule (backbone's finest +2 us).
+    // leaving each a dependent load chain of its own. With a single batch the barrier only constrains
+    // the schedule.
     if constexpr (NT > kTB) asm volatile("" ::: "memory");
     const int n16 = lane & 15, g = lane >> 4;
     const int ntile = nsp / 16;
@@ -391,7 +386,6 @@ __device__ __forceinline__ void fine_item(const FineArgs& a, const ItemHead<T, D
     float xs[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) xs[t] = 0.f;
-    uint4 vkeep[kSplitV ? NT - kTS : 1][NJ];
     auto consume_tiles = [&](int t0) {
 #pragma unroll
         for (int i = 0; i < kTB; ++i) {
@@ -424,9 +418,7 @@ __device__ __forceinline__ void fine_item(const FineArgs& a, const ItemHead<T, D
                 // (a missing candidate's row gets weight 0 in the messages)
                 const uint4 vv = (D == 32 || gok[t]) ? vc[i][j] : make_uint4(0, 0, 0, 0);
                 const int c0 = (g + 4 * j) * E;               // first channel of this chunk
-                if (kSplitV && t >= kTS) {                    // compile-time after unrolling
-                    vkeep[kSplitV ? t - kTS : 0][j] = vv;
-                } else if constexpr (kBf16) {
+                if constexpr (kBf16) {
                     uint16_t* vt = reinterpret_cast<uint16_t*>(Vb);
                     const uint32_t w4[4] = {vv.x, vv.y, vv.z, vv.w};
 #pragma unroll
@@ -605,46 +597,18 @@ __device__ __forceinline__ void fine_item(const FineArgs& a, const ItemHead<T, D
     // ---- 5b. messages on MFMA ----
     float4_t o = {0.f, 0.f, 0.f, 0.f};
     if constexpr (kBf16) {
-        // slots [s0, s0 + n) staged at Vt columns 0 .. n-1; lane half hh sums its half of them
-        auto pv_part = [&](int s0, int n) {
-            const int sph = n / NH;
-            const uint16_t* prow_l = reinterpret_cast<const uint16_t*>(Pb) + t4 * nsp + s0 + hh * sph;
-            const uint16_t* vrow_l = reinterpret_cast<const uint16_t*>(Vb) + (4 * cg + t4) * lay.vpitch + hh * sph;
-            for (int st = 0; st < sph; st += 4) {
-                const uint2 pa = *reinterpret_cast<const uint2*>(prow_l + st);
-                const uint2 vb = *reinterpret_cast<const uint2*>(vrow_l + st);
-                short4_t av, bv;
-                av[0] = static_cast<short>(pa.x); av[1] = static_cast<short>(pa.x >> 16);
-                av[2] = static_cast<short>(pa.y); av[3] = static_cast<short>(pa.y >> 16);
-                bv[0] = static_cast<short>(vb.x); bv[1] = static_cast<short>(vb.x >> 16);
-                bv[2] = static_cast<short>(vb.y); bv[3] = static_cast<short>(vb.y >> 16);
-                o = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(av, bv, o, 0, 0, 0);
-            }
-        };
-        if constexpr (kSplitV) {
-            pv_part(0, kSplitSlots);
-            // the second half's value rows over the first's (same lane layout as in the tiles)
-            wave_lds_sync();
-            uint16_t* vt = reinterpret_cast<uint16_t*>(Vb);
-#pragma unroll
-            for (int t = kTS; t < NT; ++t) {
-                if (t >= ntile) break;                        // uniform
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    const uint4 vv = vkeep[t - kTS][j];
-                    const int c0 = (g + 4 * j) * E;
-                    const uint32_t w4[4] = {vv.x, vv.y, vv.z, vv.w};
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const uint32_t bits = (e & 1) ? (w4[e >> 1] >> 16) : (w4[e >> 1] & 0xFFFFu);
-                        vt[(c0 + e) * lay.vpitch + 16 * (t - kTS) + n16] = static_cast<uint16_t>(bits);
-                    }
-                }
-            }
-            wave_lds_sync();
-            pv_part(kSplitSlots, nsp - kSplitSlots);
-        } else {
-            pv_part(0, nsp);
+        const int sph = nsp / NH;
+        const uint16_t* prow_l = reinterpret_cast<const uint16_t*>(Pb) + t4 * nsp + hh * sph;
+        const uint16_t* vrow_l = reinterpret_cast<const uint16_t*>(Vb) + (4 * cg + t4) * lay.vpitch + hh * sph;
+        for (int st = 0; st < sph; st += 4) {
+            const uint2 pa = *reinterpret_cast<const uint2*>(prow_l + st);
+            const uint2 vb = *reinterpret_cast<const uint2*>(vrow_l + st);
+            short4_t av, bv;
+            av[0] = static_cast<short>(pa.x); av[1] = static_cast<short>(pa.x >> 16);
+            av[2] = static_cast<short>(pa.y); av[3] = static_cast<short>(pa.y >> 16);
+            bv[0] = static_cast<short>(vb.x); bv[1] = static_cast<short>(vb.x >> 16);
+            bv[2] = static_cast<short>(vb.y); bv[3] = static_cast<short>(vb.y >> 16);
+            o = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(av, bv, o, 0, 0, 0);
         }
     } else {
         const int sph = nsp / NH;

@@ -181,6 +181,12 @@ struct FineArgs {
     const float* coarser_msg[QTA_MAX_LEVELS];   // entry j: message of level j (j >= 1)
     int lvl_W[QTA_MAX_LEVELS];                  // map width of level j
     int lvl_N[QTA_MAX_LEVELS];                  // tokens of level j
+    // the same by coarser level j (entry j), as the bf16 kernel's lanes read it; set by the launcher
+    struct Ancestors {
+        const float* msg;
+        int W;
+        uint32_t map_floats;                    // floats of one batch element's message
+    } anc[QTA_MAX_LEVELS];
 };
 
 // Multiscale position encoding of one level: dst += (or =, for level 0) the 3x3 depth-wise

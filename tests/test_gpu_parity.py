@@ -300,6 +300,25 @@ def test_forward_parity(dev, variant, dtype, B, H, W, heads, d, L, K):
     run_and_compare(dev, q, k, v, levels=L, K=K, variant=variant, dtype=dtype, w=w)
 
 
+@pytest.mark.parametrize("variant,weighted", [("A", False), ("B", True), ("B", False)])
+@pytest.mark.parametrize("B,H,W,heads,d,L,K,epipolar", [
+    (1, 19, 22, 1, 32, 3, 1, False),       # one tile of candidate slots, four of sixteen live
+    (2, 18, 15, 3, 64, 3, 4, False),       # one tile, full
+    (1, 19, 22, 2, 32, 3, 5, False),       # two tiles, the second partly live
+    (1, 21, 26, 3, 64, 3, 9, False),       # four tiles, d = 64
+    (1, 33, 31, 2, 32, 6, 17, False),      # eight tiles; five ancestors (two groups), odd at every level
+    (1, 22, 25, 1, 64, 3, 33, False),      # sixteen tiles, d = 64
+    (2, 3, 45, 2, 32, 6, 6, True),         # one-row maps, pairs of parents with a half-empty last pair
+    (1, 2, 37, 1, 64, 5, 20, True),        # the same with eight tiles and five ancestors
+])
+def test_bf16_slot_tiles_and_ancestors(dev, variant, weighted, B, H, W, heads, d, L, K, epipolar):
+    """The bf16 fine kernels at the edges of their slot tiles, ancestor groups and sibling groups; the
+    tolerance is the parity protocol's for bf16 storage."""
+    q, k, v = rand_qkv(7 * H + W + K, B, H, W, heads, d, "bf16")
+    w = np.random.default_rng(6).random((B, H * W, heads, L)).astype(np.float32) if weighted else None
+    run_and_compare(dev, q, k, v, levels=L, K=K, variant=variant, dtype="bf16", w=w, epipolar=epipolar)
+
+
 @pytest.mark.parametrize("variant", ["A", "B"])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_single_level_is_dense_attention(dev, variant, dtype):
