@@ -165,6 +165,26 @@ def test_pyramid_bf16_rounding_ties(dev, W):
 def test_topk_matches_full_sort(dev, rows, n, K):
     rng = np.random.default_rng(rows * n + K)
     keys = rng.integers(-20, 20, size=(rows, n)).astype(np.float32) / 4      # many exact ties
+    check_topk(dev, rng, keys, K)
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 128, 129, 257, 385, 513, 769, 1025, 1200, 1281, 1537, 2049, 3073, 4096])
+@pytest.mark.parametrize("K", [1, 16, 33, 64])
+def test_topk_slots_and_survivors(dev, n, K):
+    """Rows at the edges of the slot counts a lane holds, with distinct scores (few survivors of the bound),
+    one score throughout (every candidate survives), scores in two values, +-0 and infinities; exact."""
+    rng = np.random.default_rng(n + K)
+    keys = rng.standard_normal((6, n)).astype(np.float32)
+    keys[1] = 0.25
+    keys[2] = np.where(rng.random(n) < 0.5, 0.0, -0.0)
+    keys[3] = np.sort(keys[3])[::-1]
+    keys[4] = np.where(rng.random(n) < 0.3, np.inf, -np.inf)
+    keys[5] = np.where(np.arange(n) % 64 < 5, keys[5] + 8, keys[5])            # the best in a few lanes
+    check_topk(dev, rng, keys, K)
+
+
+def check_topk(dev, rng, keys, K):
+    rows, n = keys.shape
     names = rng.permutation(rows * n).reshape(rows, n).astype(np.int32) % (3 * n)
     names[rng.random((rows, n)) < 0.2] = -1                                    # non-candidates
     announce(f"topk rows={rows} n={n} K={K}")
