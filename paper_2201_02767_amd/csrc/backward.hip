@@ -1334,13 +1334,9 @@ hipError_t launch_bwd_level(const BwdLevelArgs& a, int d, bool variant_a, bool u
 {
     if (4 * a.Kp > 64) return hipErrorInvalidValue;
     const BwdLevelArgs b = with_divisors(a);
-    if (use_bf16) {
-        if (d == 32) return launch_level_td<bf16, 32>(b, variant_a, finest, stream);
-        if (d == 64) return launch_level_td<bf16, 64>(b, variant_a, finest, stream);
-    } else {
-        if (d == 32) return launch_level_td<float, 32>(b, variant_a, finest, stream);
-        if (d == 64) return launch_level_td<float, 64>(b, variant_a, finest, stream);
-    }
+    if (use_bf16) return launch_bwd_query_bf16(b, d, variant_a, finest, stream);
+    if (d == 32) return launch_level_td<float, 32>(b, variant_a, finest, stream);
+    if (d == 64) return launch_level_td<float, 64>(b, variant_a, finest, stream);
     return hipErrorInvalidValue;
 }
 
@@ -1368,7 +1364,9 @@ hipError_t launch_bwd_keys(const BwdLevelArgs& a, const BwdScanArgs& sc, int d, 
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const long long max_chunks = static_cast<long long>(sc.n) + (static_cast<long long>(sc.n) * a.Kp + kKeyChunk - 1) / kKeyChunk;
     const BwdLevelArgs k = with_divisors(a);
-    if (use_bf16) {
+    if (use_bf16 && finest) {
+        e = launch_bwd_key_finest_bf16(k, d, variant_a, max_chunks, stream);
+    } else if (use_bf16) {
         if (d == 32) e = launch_key_td<bf16, 32>(k, variant_a, finest, max_chunks, stream);
         else if (d == 64) e = launch_key_td<bf16, 64>(k, variant_a, finest, max_chunks, stream);
         else return hipErrorInvalidValue;

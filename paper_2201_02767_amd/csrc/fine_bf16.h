@@ -6,11 +6,11 @@
 // map); one wave owns it. Candidate slot s = 4r + c is child c of kept key r (ROW: s = 2(half*K + r) + c).
 // The slots are taken in NT tiles of 16, NT = 1, 2, 4, 8 or 16 (a power of two that covers 4K; slots past
 // 4K read the map's first row and weigh nothing).
-//   1. lane l works out the address of slot l (l + 64, ...) once; row swaps hand tile t's sixteen offsets to
-//      all four 16-lane rows. Lane 16g + n then gathers chunks g, g+4, ... of slot 16t + n: the key rows
-//      into registers, the value rows straight into the wave's LDS (no registers, no LDS write
-//      instructions), as [tile][chunk][slot of the tile] 16-byte chunks;
-//   2. logits on the 16x16x32 MFMA from the key registers; operand rows 4g .. 4g+3 are query g, so lane
+//   1. lane 4n + t works out the address of slot 16t + n (and of the slots 64 on) once and hands it to its
+//      quad, which gathers that slot's row: the key rows into registers, the value rows straight into the
+//      wave's LDS (bf16_tiles.h);
+//   2. logits on the 16x16x32 MFMA, the key chunks passed through LDS into operand lanes; operand rows
+//      4g .. 4g+3 are query g, so lane
 //      16g + n holds query g's logits of slots 16t + n for every t;
 //   3. weights: B a softmax over the row's 16 lanes and the lane's tiles (unnormalised, so that the largest
 //      weight, 1, is exact in bf16; the message is scaled by 1/sum), A over each lane quad (the children of
@@ -34,49 +34,18 @@
 #ifndef QTA_FINE_BF16_H
 #define QTA_FINE_BF16_H
 
-#include "qta_device.h"
+#include "bf16_tiles.h"
 #include "qta_internal.h"
 
 namespace qta {
 namespace fine16 {
 
-typedef float float4_t __attribute__((ext_vector_type(4)));
-typedef float float2_t __attribute__((ext_vector_type(2)));
-typedef float float2u_t __attribute__((ext_vector_type(2), aligned(4)));   // pairs at any float
-typedef short short4_t __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+using namespace tiles;
 
-// Bytes from one tile's value rows to the next in LDS: 32 past a multiple of the 256 bytes of the banks, so
-// that the 64 eight-byte pieces of a transposed read (four 16-lane groups, 64 bytes apart; four slots,
-// mostly of four tiles) fall on every bank twice, the least for 512 bytes.
-template <int D>
-constexpr int tile_bytes() { return 32 * D + 32; }
 // One wave's region: the value tiles, then 1 KB through which the key chunks pass one instruction's worth at
 // a time, and the weights after them.
 template <int D, int NT>
 constexpr int wave_bytes() { return NT * tile_bytes<D>() + (NT > 8 ? 128 * NT : 1024); }
-
-// Two floats as packed bf16 (round to nearest, ties to even).
-__device__ __forceinline__ uint32_t pack2(float lo, float hi)
-{
-    const float2_t f = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));
-}
-
-// The value that lane T of each lane quad holds, in all four lanes.
-template <int T>
-__device__ __forceinline__ uint32_t quad_broadcast(uint32_t x)
-{
-    return __builtin_amdgcn_update_dpp(0u, x, T * 0x55, 0xF, 0xF, false);
-}
-
-typedef __attribute__((address_space(3))) unsigned char lds_byte;
-
-__device__ __forceinline__ short4_t read_transposed(lds_byte* p)
-{
-    return __builtin_amdgcn_ds_read_tr16_b64_v4i16(reinterpret_cast<__attribute__((address_space(3))) short4_t*>(p));
-}
 
 template <int D, int NT, bool VA, bool FINEST, bool ROW>
 __device__ __forceinline__ void item(const FineArgs& a, const int it, unsigned char* const base)
@@ -91,7 +60,6 @@ __device__ __forceinline__ void item(const FineArgs& a, const int it, unsigned c
     lds_byte* const vlds = (lds_byte*)base;          // [tile][D / 32][16 slots][4] 16-byte chunks
     lds_byte* const plds = vlds + NT * TS;           // [query][n][t] bf16
     lds_byte* const slds = plds;                     // before the weights: the key chunks in passing
-    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 
     // ---- the item's coordinates (scalar) ----
     const int Np = a.Hp * a.Wp;
@@ -162,10 +130,7 @@ __device__ __forceinline__ void item(const FineArgs& a, const int it, unsigned c
     int flat[SPL];                                   // the slot's flat index at level l; negative: none
     uint64_t okm[SPL];                               // bit 4n + t: slot 64u + 16t + n is a candidate
     uint32_t off[NT];                                // tile t: this lane's chunk of slot 16t + (lane >> 2)
-    // lanes 4n .. 4n+3 take the four chunks of row n (a 64-byte request each; a lane per row costs the L1
-    // 46 cycles an instruction instead of 19), chunk (lane & 3) ^ (n >> 2): the order that keeps the LDS
-    // reads of whole rows and columns free of bank conflicts
-    const uint32_t chunk16 = static_cast<uint32_t>(((lane & 3) ^ (lane >> 4)) * 16);
+    const uint32_t chunk16 = gather_chunk(lane);
 #pragma unroll
     for (int u = 0; u < SPL; ++u) {
         const int s = 64 * u + own;
@@ -186,12 +151,7 @@ __device__ __forceinline__ void item(const FineArgs& a, const int it, unsigned c
         o = ok ? o : 0u;                             // a missing candidate reads the map's first row
         flat[u] = ok ? flat[u] : -1;
         okm[u] = __ballot(ok);
-        off[4 * u] = quad_broadcast<0>(o) + chunk16;
-        if constexpr (NT > 1) off[4 * u + 1] = quad_broadcast<1>(o) + chunk16;
-        if constexpr (NT > 2) {
-            off[4 * u + 2] = quad_broadcast<2>(o) + chunk16;
-            off[4 * u + 3] = quad_broadcast<3>(o) + chunk16;
-        }
+        quad_offsets<(NT < 4 ? NT : 4)>(o, chunk16, off + 4 * u);
     }
     // key rows in registers, at most four tiles at a time (more would cost occupancy)
     constexpr int kTB = NT < 4 ? NT : 4;
@@ -203,14 +163,13 @@ __device__ __forceinline__ void item(const FineArgs& a, const int it, unsigned c
             for (int j = 0; j < NJ; ++j) kc[i][j] = load_at<uint4>(kg, off[t0 + i] + 64 * j);
     };
     load_keys(0);
+    const __amdgpu_buffer_rsrc_t vres = map_resource(vg);
     // value rows into LDS: one instruction lands its lanes' chunks in lane order
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
-            __builtin_amdgcn_global_load_lds(
-                (const __attribute__((address_space(1))) void*)(vg + (off[t] + 64 * j)),
-                (__attribute__((address_space(3))) void*)(vlds + t * TS + j * 1024), 16, 0, 0);
+            load_lds16(vres, off[t], 64 * j, vlds + t * TS + j * 1024);
 
     // ---- the finest level's combination inputs. Lane 16g + n ends with query g's message at channels
     //      16 ct + n. out = w_0 m + sum over the ancestors e of w_e anc_e is a product of a 4 x E by an E x D
@@ -267,17 +226,9 @@ __device__ __forceinline__ void item(const FineArgs& a, const int it, unsigned c
         for (int i = 0; i < kTB; ++i) {
             float4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                // from the gather's lanes (quad n: row n's chunks) to the operand's (lane 16g + n: chunk g of
-                // row n) through LDS. A wave's LDS accesses complete in order, so the next chunks may
-                // overwrite these at once: only the compiler has to keep the order
-                *(__attribute__((address_space(3))) u4*)(slds + lane * 16) = __builtin_bit_cast(u4, kc[i][j]);
-                asm volatile("" ::: "memory");
-                const u4 kr = *(__attribute__((address_space(3))) u4*)(slds + n16 * 64 + ((g ^ (n16 >> 2)) * 16));
-                asm volatile("" ::: "memory");
+            for (int j = 0; j < NJ; ++j)
                 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, qa[j]),
-                                                              __builtin_bit_cast(bf16x8_t, kr), acc, 0, 0, 0);
-            }
+                                                              pass_operand(kc[i][j], slds, lane), acc, 0, 0, 0);
             xt[t0 + i] = acc[0];                                 // rows 4g .. 4g+3 are all query g
         }
     }
@@ -327,23 +278,8 @@ __device__ __forceinline__ void item(const FineArgs& a, const int it, unsigned c
         }
     }
 
-    // ---- 5a. the weights into LDS: [query g][position of n16][t]. The positions make the product's lane
-    //      groups read slots 16 bytes apart (tile_bytes) ----
-    const int pos = NT == 4 ? ((n16 & 8) | ((n16 & 3) << 1) | ((n16 >> 2) & 1))
-                  : NT == 2 ? (((n16 & 3) << 2) | ((n16 >> 3) << 1) | ((n16 >> 2) & 1)) : n16;
-    {
-        lds_byte* const pw = plds + (g * 16 + pos) * NT * 2;
-        if constexpr (NT == 1) {
-            *(__attribute__((address_space(3))) uint16_t*)pw = static_cast<uint16_t>(pack2(wt[0], 0.f));
-        } else if constexpr (NT == 2) {
-            *(__attribute__((address_space(3))) uint32_t*)pw = pack2(wt[0], wt[1]);
-        } else {
-            typedef uint32_t u2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-            for (int t = 0; t < NT; t += 4)
-                *(__attribute__((address_space(3))) u2*)(pw + t * 2) = u2{pack2(wt[t], wt[t + 1]), pack2(wt[t + 2], wt[t + 3])};
-        }
-    }
+    // ---- 5a. the weights into LDS: [query g][place of n16][t] ----
+    store_weights<NT>(plds, wt, lane);
 
     // ---- 4. this level's selection (levels above the finest): each query keeps its Ks best candidates ----
     if constexpr (!FINEST) {
@@ -397,7 +333,7 @@ __device__ __forceinline__ void item(const FineArgs& a, const int it, unsigned c
                     store_at<float>(ko, at, VA ? kvs[u][r] : scs[VA ? 0 : u][r]);
                     // A: refined at the next level (Omega)
                     if constexpr (VA)
-                        *(__attribute__((address_space(3))) uint16_t*)(plds + ((r * 16 + pos) * NT + 4 * u + g) * 2) = 0;
+                        *(lds_ptr<uint16_t>)(plds + ((r * 16 + weight_place<NT>(n16)) * NT + 4 * u + g) * 2) = 0;
                 }
                 before += __popcll(mask);
             }
@@ -407,56 +343,14 @@ __device__ __forceinline__ void item(const FineArgs& a, const int it, unsigned c
             }
         }
     }
+    wait_lds_loads();
     wave_lds_sync();
 
-    // ---- 5b. messages: contraction index i = position(n)*NT + t, 32 per MFMA (16 with one tile). Lane group
-    //      g's eight (four) indices from 32u + 8g (4g); a transposed read covers four of them ----
+    // ---- 5b. messages ----
     float4_t m4[CT];
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) m4[ct] = float4_t{0.f, 0.f, 0.f, 0.f};
-    {
-        // Lane i of a group reads eight bytes of row (index) k = i >> 2: half i & 1 of chunk 2ct + (i >> 1 & 1),
-        // which the row of slot n holds at place (chunk & 3) ^ (n >> 2). The slots of a read, by tiles:
-        //   NT = 1:  n = 4g + k                          NT = 2:  n = g + 4 (k >> 1) + 8r, t = k & 1
-        //   NT = 4:  n = g + 4 (2u + r), t = k           NT = 8:  n = g + 4u, t = k + 4r
-        //   NT = 16: n = 2u + (g >> 1), t = 8 (g & 1) + k + 4r
-        const int k = n16 >> 2, c2 = (n16 >> 1) & 1;
-        const int row_at = NT == 1 ? (4 * g + k) * 64 : NT == 2 ? (k & 1) * TS + (g + 4 * (k >> 1)) * 64
-                         : NT == 16 ? (8 * (g & 1) + k) * TS + (g >> 1) * 64 : k * TS + g * 64;
-        const int swz = NT == 1 ? c2 ^ g : NT == 2 ? c2 ^ (k >> 1) : c2;     // the lane's part of the place
-        lds_byte* const vr0 = vlds + row_at + (n16 & 1) * 8;
-        // read of channel tile ct where the rest of the place's n >> 2 is x (a constant)
-        auto read_v = [&](int ct, int x, int at) -> short4_t {
-            return read_transposed(vr0 + ((swz ^ x ^ (2 * (ct & 1))) * 16) + (ct >> 1) * 1024 + at);
-        };
-        lds_byte* const pr = plds + ((n16 >> 2) * 16 * NT + (NT == 1 ? 4 : 8) * g) * 2;
-        if constexpr (NT == 1) {
-            const short4_t p = *(__attribute__((address_space(3))) short4_t*)pr;
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
-                m4[ct] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(p, read_v(ct, 0, 0), m4[ct], 0, 0, 0);
-        } else {
-            typedef short short8_t __attribute__((ext_vector_type(8)));
-#pragma unroll
-            for (int u = 0; u < NT / 2; ++u) {
-                const short8_t p = *(__attribute__((address_space(3))) short8_t*)(pr + u * 64);
-#pragma unroll
-                for (int ct = 0; ct < CT; ++ct) {
-                    short4_t v[2];
-#pragma unroll
-                    for (int r = 0; r < 2; ++r) {
-                        if constexpr (NT == 2) v[r] = read_v(ct, 2 * r, 512 * r);
-                        else if constexpr (NT == 4) v[r] = read_v(ct, 2 * u + r, 256 * (2 * u + r));
-                        else if constexpr (NT == 8) v[r] = read_v(ct, u, 256 * u + 4 * r * TS);
-                        else v[r] = read_v(ct, u >> 1, 128 * u + 4 * r * TS);
-                    }
-                    const short8_t vv = __builtin_shufflevector(v[0], v[1], 0, 1, 2, 3, 4, 5, 6, 7);
-                    m4[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, p),
-                                                                     __builtin_bit_cast(bf16x8_t, vv), m4[ct], 0, 0, 0);
-                }
-            }
-        }
-    }
+    mma_rows<D, NT, 1>(m4, plds, 0, vlds, lane);
     // rows 4g .. 4g+3 of the product are all query g
     float m[CT];
 #pragma unroll

@@ -431,6 +431,9 @@ hipError_t launch_sort_rows(int32_t* idx, float* key, long long rows, int K, hip
 hipError_t launch_fill_zero(const FillRange* r, int n, hipStream_t stream);
 hipError_t launch_bwd_level(const BwdLevelArgs& a, int d, bool variant_a, bool use_bf16, bool finest,
                             hipStream_t stream);
+// The bf16 forms behind launch_bwd_level and launch_bwd_keys (divisors set).
+hipError_t launch_bwd_query_bf16(const BwdLevelArgs& a, int d, bool variant_a, bool finest, hipStream_t stream);
+hipError_t launch_bwd_key_finest_bf16(const BwdLevelArgs& a, int d, bool variant_a, long long max_chunks, hipStream_t stream);
 hipError_t launch_bwd_keys(const BwdLevelArgs& a, const BwdScanArgs& sc, int d, bool variant_a, bool use_bf16,
                            bool finest, hipStream_t stream);
 hipError_t launch_bwd_coarse(const BwdCoarseArgs& a, int d, bool variant_a, bool use_bf16, hipStream_t stream);

@@ -153,6 +153,25 @@ def test_backward_matches_oracle(dev, variant, dtype, B, H, W, heads, d, L, K, w
     run_backward(dev, q, k, v, g, levels=L, K=K, variant=variant, dtype=dtype, w=w, label="case")
 
 
+@pytest.mark.parametrize("variant", ["A", "B"])
+@pytest.mark.parametrize("B,H,W,heads,d,L,K", [
+    (1, 19, 22, 1, 32, 3, 1),       # one tile of candidate slots, four of sixteen live; lists of one key
+    (2, 18, 15, 3, 64, 3, 5),       # two tiles, the second partly live
+    (1, 21, 26, 3, 64, 3, 9),       # four tiles, d = 64
+    (1, 66, 47, 2, 32, 7, 16),      # four tiles full, six coarser levels (two groups in the combination), odd
+    (1, 70, 90, 1, 32, 3, 2),       # lists much longer than a chunk at some keys, empty at others
+])
+def test_backward_bf16_tiles(dev, variant, B, H, W, heads, d, L, K):
+    """The bf16 passes at the edges of their slot tiles, level groups and key lists (queries drawn near few
+    keys, so that some lists are long); the tolerance is the file's."""
+    seed = 700 + H * W + K
+    q, k, v, g = (rand(seed + i, (B, H, W, heads, d), "bf16") for i in range(4))
+    if K == 2:
+        k[:, : H // 8] *= 2         # a few keys draw most queries
+    w = np.random.default_rng(seed).random((B, H * W, heads, L)).astype(np.float32) if variant == "B" else None
+    run_backward(dev, q, k, v, g, levels=L, K=K, variant=variant, dtype="bf16", w=w, label="tiles")
+
+
 @pytest.mark.parametrize("variant,dtype", [("A", "bf16"), ("B", "f32")])
 def test_backward_epipolar(dev, variant, dtype):
     q, k, v, g = (rand(400 + i, (2, 5, 37, 2, 32), dtype) for i in range(4))
