@@ -158,6 +158,8 @@ qta_status qta_forward(const void* q, const void* k, const void* v, const float*
  *              run there, each right after its level's query pass, beside the finest key pass on
  *              aux_stream and the coarse level on `stream`; ordered and joined like aux_stream.
  *              NULL: those go to aux_stream or `stream`, whichever keeps the coarse level busier.
+ *              QuadTree-B with bf16 inputs and no position encoding runs coarse to fine on `stream` alone and
+ *              uses neither.
  *   dpe_weight, dpe_bias, dv_levels  outputs of qta_backward_ex only (the forward ignores them): with
  *              pe_weight, dpe_weight (device fp32 [levels][heads*d][3][3], 16-byte aligned) receives the
  *              gradient of the encoding's kernels, and with pe_bias, dpe_bias (device fp32
@@ -239,8 +241,8 @@ qta_status qta_forward_ex_noalloc(const void* q, const void* k, const void* v, c
  * flow into dv; with the position encoding (opt->pe_weight, Sec. 3.2) V's gradient also receives the
  * encoding's transposed stencil at every level, and opt->dpe_weight / opt->dpe_bias the gradients of
  * its kernels and bias. Unsupported (QTA_ERR_UNSUPPORTED): K_l with 4*K_l > 64 at any level, and the
- * encoding with heads*d > 256. Some sums (the message gradients of levels >= 2, and each key's list
- * of the parents that kept it) are ordered by atomics, so the last bits may vary between runs.
+ * encoding with heads*d > 256. Some sums (the message gradients of levels >= 2, or >= 3 with bf16 inputs, and
+ * each key's list of the parents that kept it) are ordered by atomics, so the last bits may vary between runs.
  * Options as in qta_forward_ex.
  */
 size_t qta_backward_workspace_bytes_ex(int B, int heads, int H, int W, int d, int levels, int K,
@@ -252,8 +254,20 @@ qta_status qta_backward_ex(const void* q, const void* k, const void* v, const fl
                            void* bwd_workspace, size_t bwd_workspace_bytes, void* stream);
 
 /*
- * qta_backward_finest_ex - the level-0 step of qta_backward_ex alone (the attention backward at the
- * finest level: its query pass and its key pass), for timing it: same arguments, and the workspaces a
+ * qta_backward_bf16_ex - qta_backward_ex for bf16 inputs with the gradients of q, k and v rounded to bf16
+ * (nearest, ties to even): dq16, dk16, dv16 are bf16 [B][H][W][heads][d], 16-byte aligned, overwritten; dq, dk,
+ * dv (fp32, as in qta_backward_ex) are scratch whose contents afterwards are unspecified. The other gradients
+ * (dw and those of the options) are fp32. levels >= 2 (QTA_ERR_UNSUPPORTED otherwise).
+ */
+qta_status qta_backward_bf16_ex(const void* q, const void* k, const void* v, const float* w, const void* dout,
+                                int B, int heads, int H, int W, int d, int levels, int K, qta_variant variant,
+                                float scale, const qta_options* opt, const void* workspace, size_t workspace_bytes,
+                                void* dq16, void* dk16, void* dv16, float* dq, float* dk, float* dv, float* dw,
+                                void* bwd_workspace, size_t bwd_workspace_bytes, void* stream);
+
+/*
+ * qta_backward_finest_ex - the level-0 step of qta_backward_ex alone (the combination's backward and the
+ * attention backward at the finest level: its query pass and its key pass), for timing it: same arguments, and the workspaces a
  * qta_backward_ex call on the same inputs left behind. It overwrites dq, dk, dv and, for QuadTree-B
  * with w, dw[..][0] with that step's values, so the gradients are no longer those of the layer
  * afterwards. levels >= 2.

@@ -593,13 +593,14 @@ __device__ __forceinline__ void block_scan_256x4(int2 (&v)[4], int2& total)
     }
 }
 
-__device__ __forceinline__ int chunks_of(int n) { return n > 0 ? (n + kKeyChunk - 1) / kKeyChunk : 1; }
+// Chunks of a list of n parents (`chunk` a power of two; an empty list has one, which writes zeros).
+__device__ __forceinline__ int chunks_of(int n, int chunk) { return n > 0 ? (n + chunk - 1) >> (31 - __clz(chunk)) : 1; }
 
 // (count, chunk count) of the key slots i0 .. i0+3 (i0 a multiple of 4) from one 16-byte load, and
 // (0, 0) past the last slot. The count array is padded to a multiple of four slots, so the load
 // (clamped to the last quad) stays inside it; it is unconditional and masked rather than selected,
 // so that the compiler keeps every such load of a thread in flight at once.
-__device__ __forceinline__ void quad_counts(const int32_t* count, int i0, int n, int2 (&c)[4])
+__device__ __forceinline__ void quad_counts(const int32_t* count, int i0, int n, int chunk, int2 (&c)[4])
 {
     const int4 r = *reinterpret_cast<const int4*>(count + min(i0, (n - 1) & ~3));
     const int v[4] = {r.x, r.y, r.z, r.w};
@@ -607,7 +608,7 @@ __device__ __forceinline__ void quad_counts(const int32_t* count, int i0, int n,
     for (int e = 0; e < 4; ++e) {
         const int valid = i0 + e < n;
         const int x = v[e] & -valid;
-        c[e] = make_int2(x, chunks_of(x) & -valid);
+        c[e] = make_int2(x, chunks_of(x, chunk) & -valid);
     }
 }
 
@@ -627,7 +628,7 @@ __device__ __forceinline__ void store_quad(int32_t* p, int i0, int n, int x, int
 __global__ __launch_bounds__(256) void bwd_scan_reduce_kernel(BwdScanArgs a)
 {
     int2 v[4];
-    quad_counts(a.count, blockIdx.x * 1024 + threadIdx.x * 4, a.n, v);
+    quad_counts(a.count, blockIdx.x * 1024 + threadIdx.x * 4, a.n, a.chunk, v);
     int2 total;
     block_scan_256x4(v, total);
     if (threadIdx.x == 0) {
@@ -636,55 +637,47 @@ __global__ __launch_bounds__(256) void bwd_scan_reduce_kernel(BwdScanArgs a)
     }
 }
 
-// One block: exclusive scan of the block sums, in place.
-__global__ __launch_bounds__(256) void bwd_scan_blocks_kernel(BwdScanArgs a)
+// The sum of the first n blocks' (counts, chunks), in every thread of a block of 256.
+__device__ __forceinline__ int2 sums_before(const int32_t* sums, int n)
 {
-    int2 carry = make_int2(0, 0);
-    for (int t0 = 0; t0 < a.nblocks; t0 += 1024) {
-        int2 v[4];
-        const int base = t0 + threadIdx.x * 4;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int i = base + e;
-            const int j = 2 * min(i, a.nblocks - 1);
-            const int2 b = make_int2(a.block_sums[j], a.block_sums[j + 1]);
-            v[e] = i < a.nblocks ? b : make_int2(0, 0);
-        }
-        int2 total;
-        block_scan_256x4(v, total);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int i = base + e;
-            if (i < a.nblocks) {
-                a.block_sums[2 * i] = v[e].x + carry.x;
-                a.block_sums[2 * i + 1] = v[e].y + carry.y;
-            }
-        }
-        carry.x += total.x;
-        carry.y += total.y;
+    __shared__ int2 part[4];
+    int2 t = make_int2(0, 0);
+    for (int i = threadIdx.x; i < n; i += 256) {
+        const int2 s = reinterpret_cast<const int2*>(sums)[i];
+        t.x += s.x;
+        t.y += s.y;
     }
-    if (threadIdx.x == 0) {
-        a.off[a.n] = carry.x;
-        a.coff[a.n] = carry.y;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        t.x += __shfl_xor(t.x, o, kWave);
+        t.y += __shfl_xor(t.y, o, kWave);
     }
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = t;
+    __syncthreads();
+    return make_int2(part[0].x + part[1].x + part[2].x + part[3].x, part[0].y + part[1].y + part[2].y + part[3].y);
 }
 
 // Per block: the exclusive scans of the counts (list offsets) and of the chunk counts, and the
-// kept key of every chunk.
+// kept key of every chunk. Each block adds up the sums of the blocks before it itself (a scan of them in a
+// kernel of its own took 5 us at every level).
 __global__ __launch_bounds__(256) void bwd_scan_write_kernel(BwdScanArgs a)
 {
     int2 v[4], c[4];
     const int base = blockIdx.x * 1024 + threadIdx.x * 4;
-    quad_counts(a.count, base, a.n, c);
+    quad_counts(a.count, base, a.n, a.chunk, c);
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = c[e];
     int2 total;
     block_scan_256x4(v, total);
-    const int2 bo = make_int2(a.block_sums[2 * blockIdx.x], a.block_sums[2 * blockIdx.x + 1]);
+    const int2 bo = sums_before(a.block_sums, static_cast<int>(blockIdx.x));
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         v[e].x += bo.x;
         v[e].y += bo.y;
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        a.off[a.n] = bo.x + total.x;
+        a.coff[a.n] = bo.y + total.y;
     }
     store_quad(a.off, base, a.n, v[0].x, v[1].x, v[2].x, v[3].x);
     store_quad(a.coff, base, a.n, v[0].y, v[1].y, v[2].y, v[3].y);
@@ -696,7 +689,7 @@ __global__ __launch_bounds__(256) void bwd_scan_write_kernel(BwdScanArgs a)
 }
 
 // Up to kSingleScanMax key slots: the whole scan in one workgroup of 1024 threads (four tiles of
-// 4096 slots), in place of the three-kernel scan. Every load comes first and every store last: a
+// 4096 slots), in place of the two-kernel scan. Every load comes first and every store last: a
 // store issued between two waits for loads would be waited for too.
 constexpr int kSingleScanMax = 16384;
 
@@ -707,7 +700,7 @@ __global__ __launch_bounds__(1024) void bwd_scan_single_kernel(BwdScanArgs a)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int2 c[4][4];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) quad_counts(a.count, t * kTile + tid * 4, a.n, c[t]);
+    for (int t = 0; t < 4; ++t) quad_counts(a.count, t * kTile + tid * 4, a.n, a.chunk, c[t]);
     int2 x[4][4];                                             // exclusive scans (list offset, first chunk)
     int2 carry = make_int2(0, 0);
 #pragma unroll
@@ -1170,36 +1163,47 @@ __global__ __launch_bounds__(64) void bwd_key_kernel(BwdLevelArgs a)
     }
 }
 
-// Keys whose list spans several chunks: the sum of the chunks' partial rows. One thread per
-// (kept-key slot, child, 4 channels).
+// Keys whose list spans several chunks: the sum of the chunks' partial rows, a wave per key, its lanes the
+// 16-byte pieces of a chunk's rows.
 __global__ __launch_bounds__(256) void bwd_key_reduce_kernel(BwdLevelArgs a, int d)
 {
     const int Np = a.Hp * a.Wp;
-    const long long n = static_cast<long long>(a.B) * a.heads * Np;
-    const int q4n = d / 4;
-    const long long tid = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (tid >= n * 4 * q4n) return;
-    const int qd = static_cast<int>(tid % q4n);
-    const int c = static_cast<int>((tid / q4n) % 4);
-    const int key = static_cast<int>(tid / (4LL * q4n));
+    const int n = a.B * a.heads * Np;                         // below 2^31 / 64 (checked by the host)
+    const int lane = threadIdx.x & 63;
+    const int key = static_cast<int>(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    if (key >= n) return;                                     // whole wave
     const int first = a.coff[key], nch = a.coff[key + 1] - first;
     if (nch <= 1) return;
     const int bh = fast_div(key, a.div_Np), J = key - bh * Np;
     const int b = fast_div(bh, a.div_heads), h = bh - b * a.heads;
     const int Jy = fast_div(J, a.div_Wp), Jx = J - Jy * a.Wp;
-    const int y = 2 * Jy + (c >> 1), x = 2 * Jx + (c & 1);
-    if (y >= a.H || x >= a.W) return;
-    float4 sk = make_float4(0.f, 0.f, 0.f, 0.f), sv = sk;
-    for (int t = 0; t < nch; ++t) {
-        const float* pk = a.partial + ((static_cast<size_t>(first + t) * 4 + c) * 2) * d + 4 * qd;
-        const float4 k4 = *reinterpret_cast<const float4*>(pk);
-        const float4 v4 = *reinterpret_cast<const float4*>(pk + d);
-        sk.x += k4.x; sk.y += k4.y; sk.z += k4.z; sk.w += k4.w;
-        sv.x += v4.x; sv.y += v4.y; sv.z += v4.z; sv.w += v4.w;
+    // a chunk's rows are [4 children][dk, dv][d]: 2d pieces of four floats
+    for (int it = lane; it < 2 * d; it += kWave) {
+        const float* p = a.partial + static_cast<size_t>(first) * 8 * d + 4 * it;
+        float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int t = 0; t < nch; ++t) {
+            const float4 x = *reinterpret_cast<const float4*>(p + static_cast<size_t>(t) * 8 * d);
+            s.x += x.x; s.y += x.y; s.z += x.z; s.w += x.w;
+        }
+        const int pieces = d / 4;
+        const int row = it / pieces, c = row >> 1, ch = 4 * (it - row * pieces);
+        const int y = 2 * Jy + (c >> 1), x = 2 * Jx + (c & 1);
+        if (y >= a.H || x >= a.W) continue;
+        const size_t at = (static_cast<size_t>(b) * a.H * a.W + y * a.W + x) * a.C + h * d + ch;
+        if (!(row & 1)) s = make_float4(a.scale * s.x, a.scale * s.y, a.scale * s.z, a.scale * s.w);
+        const float* const up = (row & 1) ? a.up_v : a.up_k;
+        if (up) {
+            const float f = child_share(Jy, Jx, a.H, a.W);
+            const float4 u = *reinterpret_cast<const float4*>(up + (static_cast<size_t>(b) * Np + J) * a.C + h * d + ch);
+            s.x += f * u.x; s.y += f * u.y; s.z += f * u.z; s.w += f * u.w;
+        }
+        float* const dst = (row & 1) ? a.dv : a.dk;
+        if (a.out_bf16)
+            *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(dst) + at) =
+                make_uint2(f32_to_bf16_bits(s.x) | (f32_to_bf16_bits(s.y) << 16), f32_to_bf16_bits(s.z) | (f32_to_bf16_bits(s.w) << 16));
+        else
+            *reinterpret_cast<float4*>(dst + at) = s;
     }
-    const size_t row = (static_cast<size_t>(b) * a.H * a.W + y * a.W + x) * a.C + h * d + 4 * qd;
-    *reinterpret_cast<float4*>(a.dk + row) = make_float4(a.scale * sk.x, a.scale * sk.y, a.scale * sk.z, a.scale * sk.w);
-    *reinterpret_cast<float4*>(a.dv + row) = sv;
 }
 
 template <typename T, int D, bool VA, bool FINEST>
@@ -1239,7 +1243,8 @@ __global__ __launch_bounds__(256) void bwd_unpool_kernel(BwdUnpoolArgs a)
     const int m = blockIdx.y;
     // given V levels are not pooled from v: their gradients are returned as they are, and v's level-0
     // gradient receives nothing from them
-    if (m == 2 && !a.v_pooled) return;                        // whole block
+    const int L = m == 2 && !a.v_pooled ? 1 : a.L;
+    if (L == 1 && !a.out16[m]) return;                        // whole block
     const int cpt = a.C / 4;
     const int n1 = a.H[1] * a.W[1] * cpt;
     const int b = static_cast<int>(blockIdx.x) / a.bpb;
@@ -1268,13 +1273,13 @@ __global__ __launch_bounds__(256) void bwd_unpool_kernel(BwdUnpoolArgs a)
     float fl = 1.0f;
 #pragma unroll
     for (int l0 = 1; l0 < LMAX; l0 += kGroup) {
-        if (l0 >= a.L) break;                                 // uniform
+        if (l0 >= L) break;                                   // uniform
         float4 g[kGroup];
         float f[kGroup];
 #pragma unroll
         for (int j = 0; j < kGroup; ++j) {
             const int l = l0 + j;
-            if (l >= LMAX || l >= a.L) break;                 // uniform
+            if (l >= LMAX || l >= L) break;                   // uniform
             const int yl = y1 >> (l - 1), xl = x1 >> (l - 1);
             const int ny = (2 * yl + 1 < a.H[l - 1]) ? 2 : 1, nx = (2 * xl + 1 < a.W[l - 1]) ? 2 : 1;
             fl *= 1.0f / static_cast<float>(ny * nx);
@@ -1286,7 +1291,7 @@ __global__ __launch_bounds__(256) void bwd_unpool_kernel(BwdUnpoolArgs a)
         }
 #pragma unroll
         for (int j = 0; j < kGroup; ++j) {
-            if (l0 + j >= LMAX || l0 + j >= a.L) break;       // uniform
+            if (l0 + j >= LMAX || l0 + j >= L) break;         // uniform
             s.x += f[j] * g[j].x;
             s.y += f[j] * g[j].y;
             s.z += f[j] * g[j].z;
@@ -1294,9 +1299,15 @@ __global__ __launch_bounds__(256) void bwd_unpool_kernel(BwdUnpoolArgs a)
         }
     }
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
-        if (ok[c])
-            *reinterpret_cast<float4*>(dst + base + tok[c]) = make_float4(r[c].x + s.x, r[c].y + s.y, r[c].z + s.z, r[c].w + s.w);
+    for (int c = 0; c < 4; ++c) {
+        if (!ok[c]) continue;
+        const float4 v = make_float4(r[c].x + s.x, r[c].y + s.y, r[c].z + s.z, r[c].w + s.w);
+        if (a.out16[m])                                       // uniform
+            *reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out16[m]) + base + tok[c]) =
+                make_uint2(f32_to_bf16_bits(v.x) | (f32_to_bf16_bits(v.y) << 16), f32_to_bf16_bits(v.z) | (f32_to_bf16_bits(v.w) << 16));
+        else
+            *reinterpret_cast<float4*>(dst + base + tok[c]) = v;
+    }
 }
 
 }  // namespace
@@ -1329,6 +1340,11 @@ BwdLevelArgs with_divisors(const BwdLevelArgs& a)
     return b;
 }
 
+hipError_t launch_bwd_combine(const BwdLevelArgs& a, int d, bool variant_a, bool use_bf16, hipStream_t stream)
+{
+    return use_bf16 ? launch_bwd_combine_bf16(with_divisors(a), d, variant_a, stream) : hipSuccess;
+}
+
 hipError_t launch_bwd_level(const BwdLevelArgs& a, int d, bool variant_a, bool use_bf16, bool finest,
                             hipStream_t stream)
 {
@@ -1340,10 +1356,14 @@ hipError_t launch_bwd_level(const BwdLevelArgs& a, int d, bool variant_a, bool u
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_bwd_keys(const BwdLevelArgs& a, const BwdScanArgs& sc, int d, bool variant_a, bool use_bf16,
-                           bool finest, hipStream_t stream)
+// Parents per chunk of the key pass.
+int key_chunk_parents(bool use_bf16) { return use_bf16 ? kKeyGroup : kKeyChunk; }
+
+hipError_t launch_bwd_sort(const BwdLevelArgs& a, const BwdScanArgs& sc_in, bool use_bf16, hipStream_t stream)
 {
-    if (sc.n <= 0) return hipErrorInvalidValue;
+    if (sc_in.n <= 0) return hipErrorInvalidValue;
+    BwdScanArgs sc = sc_in;
+    sc.chunk = key_chunk_parents(use_bf16);
     hipError_t e;
     if (sc.n <= kSingleScanMax) {
         hipLaunchKernelGGL(bwd_scan_single_kernel, dim3(1), dim3(1024), 0, stream, sc);
@@ -1352,8 +1372,6 @@ hipError_t launch_bwd_keys(const BwdLevelArgs& a, const BwdScanArgs& sc, int d, 
         const unsigned nb = static_cast<unsigned>(sc.nblocks);
         hipLaunchKernelGGL(bwd_scan_reduce_kernel, dim3(nb), dim3(256), 0, stream, sc);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(bwd_scan_blocks_kernel, dim3(1), dim3(256), 0, stream, sc);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
         hipLaunchKernelGGL(bwd_scan_write_kernel, dim3(nb), dim3(256), 0, stream, sc);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
@@ -1361,24 +1379,22 @@ hipError_t launch_bwd_keys(const BwdLevelArgs& a, const BwdScanArgs& sc, int d, 
     const long long fb = (f.nentries + 255) / 256;
     if (fb >= 0x7FFFFFFFLL) return hipErrorInvalidValue;
     hipLaunchKernelGGL(bwd_fill_kernel, dim3(static_cast<unsigned>(fb)), dim3(256), 0, stream, f);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    const long long max_chunks = static_cast<long long>(sc.n) + (static_cast<long long>(sc.n) * a.Kp + kKeyChunk - 1) / kKeyChunk;
+    return hipGetLastError();
+}
+
+hipError_t launch_bwd_keys(const BwdLevelArgs& a, int d, bool variant_a, bool use_bf16, bool finest, hipStream_t stream)
+{
+    hipError_t e;
+    const long long n = static_cast<long long>(a.B) * a.heads * a.Hp * a.Wp;
+    const int chunk = key_chunk_parents(use_bf16);
+    const long long max_chunks = n + (n * a.Kp + chunk - 1) / chunk;
     const BwdLevelArgs k = with_divisors(a);
-    if (use_bf16 && finest) {
-        e = launch_bwd_key_finest_bf16(k, d, variant_a, max_chunks, stream);
-    } else if (use_bf16) {
-        if (d == 32) e = launch_key_td<bf16, 32>(k, variant_a, finest, max_chunks, stream);
-        else if (d == 64) e = launch_key_td<bf16, 64>(k, variant_a, finest, max_chunks, stream);
-        else return hipErrorInvalidValue;
-    } else {
-        if (d == 32) e = launch_key_td<float, 32>(k, variant_a, finest, max_chunks, stream);
-        else if (d == 64) e = launch_key_td<float, 64>(k, variant_a, finest, max_chunks, stream);
-        else return hipErrorInvalidValue;
-    }
+    if (use_bf16) e = launch_bwd_key_bf16(k, d, variant_a, finest, max_chunks, stream);
+    else if (d == 32) e = launch_key_td<float, 32>(k, variant_a, finest, max_chunks, stream);
+    else if (d == 64) e = launch_key_td<float, 64>(k, variant_a, finest, max_chunks, stream);
+    else return hipErrorInvalidValue;
     if (e != hipSuccess) return e;
-    const long long rb = (static_cast<long long>(sc.n) * 4 * (d / 4) + 255) / 256;
-    if (rb >= 0x7FFFFFFFLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(bwd_key_reduce_kernel, dim3(static_cast<unsigned>(rb)), dim3(256), 0, stream, k, d);
+    hipLaunchKernelGGL(bwd_key_reduce_kernel, dim3(static_cast<unsigned>((n + 3) / 4)), dim3(256), 0, stream, k, d);
     return hipGetLastError();
 }
 

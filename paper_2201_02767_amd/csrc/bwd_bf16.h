@@ -1,6 +1,6 @@
 // The finer levels' backward passes for bf16 maps (step 2 of backward.hip), on the row tiles of bf16_tiles.h:
-// the query pass of every finer level, and the finest level's key pass. backward.hip holds the fp32 forms and
-// the coarser levels' key pass, with the derivation.
+// the combination's backward, and the finer levels' query and key passes. backward.hip holds the fp32 forms,
+// with the derivation.
 //
 // Both passes contract fp32 weights (the logit gradients, the value weights) with bf16 rows. The weights are
 // split exactly into three bf16 terms (8 + 8 + 8 bits), whose products with a bf16 row are exact in the
@@ -8,10 +8,13 @@
 //
 // What bounds them, before -> now: the previous forms gathered with a lane per row (46 cycles of the L1 an
 // instruction, see bf16_tiles.h) and read the rows back from LDS two bytes at a time, one fp32 4x4 MFMA per
-// slot. Finest level, 200x336 maps, 2 x 32 channels, K = 16, batch 2: query pass 125 -> 98 us, key pass 147 -> 99;
-// 32 maps of 56x56, 1 x 64, K = 8: query pass 50 -> 38, key pass 69 -> 35.
+// slot. Finest level, 200x336 maps, 2 x 32 channels, K = 16, batch 2: query pass 125 us with the combination's
+// backward -> 67 and 21 for that, key pass with its reduction 172 -> 105; 32 maps of 56x56, 1 x 64, K = 8:
+// query pass 50 -> 25 and 12, key pass 76 -> 42.
 #ifndef QTA_BWD_BF16_H
 #define QTA_BWD_BF16_H
+
+#include <type_traits>
 
 #include "bf16_tiles.h"
 #include "qta_internal.h"
@@ -59,6 +62,29 @@ __device__ __forceinline__ void store_split(lds_byte* w, const float (&x)[NT], i
         *(lds_ptr<u32x2_t>)p = u32x2_t{s.hi, r.hi};
         *(lds_ptr<u32x2_t>)(p + PB) = u32x2_t{s.mid, r.mid};
         *(lds_ptr<u32x2_t>)(p + 2 * PB) = u32x2_t{s.lo, r.lo};
+    }
+}
+
+// Lane 16g + n's row values at channels 16 ct + n to element `at` of the map at `base`, in fp32 or (MAY16 and
+// `half`, uniform) bf16: neighbouring lanes then trade a channel per two tiles for four-byte stores.
+template <int D, bool MAY16>
+__device__ __forceinline__ void store_row(float* map, bool half, size_t base, uint32_t at, const float (&x)[D / 16], bool on, int lane)
+{
+    const int n16 = lane & 15;
+    if (MAY16 && half) {                                      // uniform
+        unsigned char* const b = reinterpret_cast<unsigned char*>(map) + base * 2;
+        const bool odd = (lane & 1) != 0;
+        const uint32_t to = (at + (odd ? n16 + 15 : n16)) * 2u;
+#pragma unroll
+        for (int ct = 0; ct < D / 16; ct += 2) {
+            const float r = xchg_f32<1>(odd ? x[ct] : x[ct + 1]);
+            const uint32_t v = pack2(odd ? r : x[ct], odd ? x[ct + 1] : r);
+            if (on) store_at<uint32_t>(b, to + 32 * ct, v);
+        }
+    } else if (on) {
+        float* const b = map + base;
+#pragma unroll
+        for (int ct = 0; ct < D / 16; ++ct) store_at<float>(b, (at + n16) * 4u + 64 * ct, x[ct]);
     }
 }
 
@@ -170,6 +196,15 @@ __device__ __forceinline__ void query_item(const BwdLevelArgs& a, const int it, 
         flat = ok ? flat : -1;
         okm = __ballot(ok);
         quad_offsets<NT>(o, gather_chunk(lane), off);
+    }
+    // the parent's total gradient of q (without one, the first kept key is read in its place, unused)
+    float up[CT];
+    const float share = child_share(Py, Px, H, W);
+    {
+        const float* ub = a.up_q ? a.up_q + (static_cast<size_t>(b) * Np + P) * C + h * D : reinterpret_cast<const float*>(a.parent_idx);
+        const uint32_t at = a.up_q ? static_cast<uint32_t>(n16 * 4) : 0u;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) up[ct] = load_at<float>(ub, at + (a.up_q ? 64u * ct : 0u));
     }
     uint4 vc[NT][NJ];
 #pragma unroll
@@ -292,7 +327,7 @@ __device__ __forceinline__ void query_item(const BwdLevelArgs& a, const int it, 
         }
     }
 
-    // ---- dq = scale * sum_s dx_s k_s ----
+    // ---- dq = scale * sum_s dx_s k_s, plus the parent's share ----
     store_split<NT>(work, dx, lane);
     wave_lds_sync();
     {
@@ -300,151 +335,329 @@ __device__ __forceinline__ void query_item(const BwdLevelArgs& a, const int it, 
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) o[ct] = float4_t{0.f, 0.f, 0.f, 0.f};
         mma_rows<D, NT, 3>(o, work, 128 * NT, klds, lane);
-        if (qv) {
-            float* const dq_b = a.dq + static_cast<size_t>(b) * N * C + h * D;
-            const uint32_t at = (qpos * static_cast<uint32_t>(C) + n16) * 4u;
+        float dq[CT];
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct) store_at<float>(dq_b, at + 64 * ct, a.scale * o[ct][0]);
-        }
+        for (int ct = 0; ct < CT; ++ct) dq[ct] = a.up_q ? a.scale * o[ct][0] + share * up[ct] : a.scale * o[ct][0];
+        store_row<D, FINEST>(a.dq, FINEST && a.out_bf16, static_cast<size_t>(b) * N * C + h * D, qpos * static_cast<uint32_t>(C), dq,
+                             qv, lane);
     }
 
-    // ---- level 0: the combination's backward. The four queries share one ancestor at every level j >= 1 (at
-    //      j = 1 it is P itself): dm^j receives sum_r w_{r,j} dout_r, written at j = 1 and added with atomics
-    //      above, and dw_{r,j} = <dout_r, m^j>. Four levels at a time: the fp32 MFMA sums over the queries
-    //      (operand lane 16g + n: w of query g at level n >> 2, and dout of query g at channel n), so that
-    //      lane group g ends with its level's sums; for dw, lane group g's messages go to all groups. ----
-    if constexpr (FINEST) {
-        const int L = a.levels;
-        const bool want_dw = !VA && a.w && a.dw;              // uniform
-        float dv[CT];                                         // dout of query g, zero off the map
-        {
-            const unsigned char* db = static_cast<const unsigned char*>(a.dout) + (static_cast<size_t>(b) * N * C + h * D) * 2;
-            const uint32_t at = __umul24(qpos, tok_bytes) + static_cast<uint32_t>(n16 * 2);
+    // (the rest of dw, and the coarser levels' message gradients: combine_item)
+    if constexpr (FINEST && !VA) {
+        if (a.w && a.dw && n16 == 0 && qv) store_at<float>(a.dw + wq_off, wrow * 4u, dw0);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// the combination's backward
+// ---------------------------------------------------------------------------------------------
+
+// x plus the other lane's x, for the lane at distance 8, 16 or 32.
+template <int M>
+__device__ __forceinline__ float add_across(float x)
+{
+    const uint32_t u = __float_as_uint(x);
+    if constexpr (M == 8) {
+        return x + __uint_as_float(__builtin_amdgcn_update_dpp(0u, u, kDppRowRor8, 0xF, 0xF, false));
+    } else if constexpr (M == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    } else {
+        static_assert(M == 32, "distance");
+        const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+}
+
+// The sum over each aligned group of G = 8 or 16 lanes, in all of them.
+template <int G>
+__device__ __forceinline__ float add_group(float x)
+{
+    auto step = [](float v, auto ctrl) {
+        return v + __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), decltype(ctrl)::value, 0xF, 0xF, false));
+    };
+    x = step(x, std::integral_constant<int, kDppXor1>());
+    x = step(x, std::integral_constant<int, kDppXor2>());
+    x = step(x, std::integral_constant<int, kDppRowHalfMirror>());
+    if constexpr (G == 16) x = step(x, std::integral_constant<int, kDppRowMirror>());
+    return x;
+}
+
+// dm^l of every level l >= 1 sums w_{i,l} dout_i over a token's level-0 descendants i, and dw_{i,l} =
+// <dout_i, m^l of the ancestor>. One wave takes one head of a block of neighbouring parents (level-1 tokens;
+// 4x2 with d = 32, 2x2 with d = 64, a run on one-row maps): lane Q i + e has channels 4e .. 4e+3 of parent i's
+// four tokens. A level's sums go over the block in registers, and are stored where the block holds all of a
+// token's descendants (levels 1 and 2; 1 to 4 on one-row maps) and added with atomics above. Bound by the
+// latency of one wave's loads (few waves). Inside the query pass, a wave per parent, it took 31 of that pass's
+// 98 us (200x336, 2 x 32, batch 2) and 13 of 38 (32 x 56x56, 1 x 64), with eight times the atomics; alone 21
+// and 12, and the coarser levels no longer wait for the finest.
+struct CombineGrid {
+    FastDiv div_map, div_row;           // blocks of parents per map and per row of blocks
+};
+
+template <int D, bool VA, bool ROW>
+__device__ __forceinline__ void combine_item(const BwdLevelArgs& a, const CombineGrid& cg, const int it)
+{
+    constexpr int Q = D / 4;                                  // lanes per parent
+    constexpr int NP = 64 / Q;                                // parents per wave
+    constexpr int RX = ROW ? NP : NP == 8 ? 4 : 2, RY = NP / RX;
+    const int lane = threadIdx.x & 63;
+    const int e = lane & (Q - 1), i = lane / Q;
+    const int blk = fast_div(it, a.div_heads), h = it - blk * a.heads;
+    const int b = fast_div(blk, cg.div_map), br = blk - b * cg.div_map.d;
+    const int y0 = fast_div(br, cg.div_row), x0 = br - y0 * cg.div_row.d;
+    // the bits of i: x, then y, then x again, so that 2x2 parents are four neighbours
+    const int Px = x0 * RX + (ROW ? i : (i & 1) | ((i >> 1) & 2)), Py = ROW ? 0 : y0 * RY + ((i >> 1) & 1);
+    const bool pv = Px < a.Wp && Py < a.Hp;
+    const int H = a.H, W = a.W, C = a.C, L = a.levels;
+    const int N = H * W;
+    const bool want_dw = !VA && a.w && a.dw;                  // uniform
+    const unsigned char* db = static_cast<const unsigned char*>(a.dout) + (static_cast<size_t>(b) * N * C + h * D) * 2;
+    const float* const wb = a.w ? a.w + (static_cast<size_t>(b) * N * a.heads + h) * L : nullptr;
+    float g[4][4];                                            // dout of token q, zero off the map
+    uint32_t wrow[4];
+    bool qv[4];
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct) dv[ct] = qv ? bf16_bits_to_f32(load_at<uint16_t>(db, at + 32 * ct)) : 0.f;
+    for (int q = 0; q < 4; ++q) {
+        const int y = 2 * Py + (q >> 1), x = 2 * Px + (q & 1);
+        qv[q] = pv && y < H && x < W;
+        const uint32_t tok = static_cast<uint32_t>(__mul24(min(y, H - 1), W) + min(x, W - 1));
+        wrow[q] = tok * static_cast<uint32_t>(a.heads * L);
+        const unsigned m = opaque_mask(qv[q]);
+        const uint2 r = load_at<uint2>(db, __umul24(tok, static_cast<uint32_t>(C * 2)) + static_cast<uint32_t>(e * 8));
+        g[q][0] = low_half(r.x & m);
+        g[q][1] = high_half(r.x & m);
+        g[q][2] = low_half(r.y & m);
+        g[q][3] = high_half(r.y & m);
+    }
+    for (int l0 = 1; l0 < L; l0 += 4) {                       // uniform: four levels at a time
+        // w of the four levels by token: 16 bytes at a level that leaves them inside the row (rows of two or
+        // three levels: 8 bytes)
+        float w[4][4];
+        if (!VA && a.w) {                                     // uniform
+            typedef float float4u_t __attribute__((ext_vector_type(4), aligned(4)));
+            typedef float float2u_t __attribute__((ext_vector_type(2), aligned(4)));
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (L >= 4) {                                 // uniform
+                    const int from = min(l0, L - 4), sh = l0 - from;
+                    const float4u_t v = load_at<float4u_t>(wb, (wrow[q] + from) * 4u);
+                    w[q][0] = sh == 0 ? v[0] : sh == 1 ? v[1] : sh == 2 ? v[2] : v[3];
+                    w[q][1] = sh == 0 ? v[1] : sh == 1 ? v[2] : v[3];
+                    w[q][2] = sh == 0 ? v[2] : v[3];
+                    w[q][3] = v[3];
+                } else {
+                    const float2u_t v = load_at<float2u_t>(wb, (wrow[q] + L - 2) * 4u);    // levels L-2, L-1
+                    w[q][0] = L == 3 ? v[0] : v[1];
+                    w[q][1] = w[q][2] = w[q][3] = v[1];
+                }
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) w[q][j] = VA ? 1.f : 1.0f / L;
         }
-        if (want_dw && n16 == 0 && qv) store_at<float>(a.dw + wq_off, wrow * 4u, dw0);
-        for (int l0 = 1; l0 < L; l0 += 4) {                   // uniform
-            const int wlev = l0 + (n16 >> 2);                 // this lane's level as an operand row
-            float wl = VA ? 1.f : 1.0f / L;
-            if constexpr (!VA) {
-                if (a.w) wl = load_at<float>(a.w + wq_off, (wrow + min(wlev, L - 1)) * 4u);   // uniform
-            }
-            // lane group g's level: the ancestor's row in its dm and in the forward's message
-            const int lev = min(l0 + g, L - 1);
-            const size_t arow = static_cast<size_t>(b) * a.lvl_N[lev] +
-                                static_cast<size_t>((2 * Py) >> lev) * a.lvl_W[lev] + ((2 * Px) >> lev);
-            const size_t at = (arow * a.heads + h) * D + n16;
-            float mm[CT];
+        float4_t m[4];
+        uint32_t row[4];                                      // bytes within a batch element's messages (below 2^32)
+        size_t map[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int l = min(l0 + j, L - 1);                 // uniform; clamped: unused past L-1
+            const int y = min(Py, a.Hp - 1) >> (l - 1), x = min(Px, a.Wp - 1) >> (l - 1);
+            row[j] = (static_cast<uint32_t>(__mul24(y, a.lvl_W[l]) + x) * static_cast<uint32_t>(C) +
+                      static_cast<uint32_t>(h * D + 4 * e)) * 4u;
+            map[j] = static_cast<size_t>(b) * static_cast<uint32_t>(a.lvl_N[l]) * static_cast<uint32_t>(C);
+            if (want_dw) m[j] = load_at<float4_t>(a.msg_fwd[l] + map[j], row[j]);
+        }
+        float part[4][4];                                     // dw of token q, level l0 + j
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int l = min(l0 + j, L - 1);                 // uniform; past L-1 nothing is stored
+            float4_t s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) s[c] += w[q][j] * g[q][c];
             if (want_dw) {
 #pragma unroll
-                for (int ct = 0; ct < CT; ++ct) mm[ct] = a.msg_fwd[lev][at + 16 * ct];
+                for (int q = 0; q < 4; ++q)
+                    part[q][j] = add_group<Q>(g[q][0] * m[j][0] + g[q][1] * m[j][1] + g[q][2] * m[j][2] + g[q][3] * m[j][3]);
             }
-            float4_t s[CT];
+            // over the block's parents that share the level-l ancestor
+            int bits = 0;                                     // of i, summed over
+            if (l >= 2) {                                     // uniform
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct) {
-                s[ct] = float4_t{0.f, 0.f, 0.f, 0.f};
-                s[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(wl, dv[ct], s[ct], 0, 0, 0);
-            }
-            if (l0 + g < L) {
-                float* const dst = a.dm_out[lev] + at;
+                for (int c = 0; c < 4; ++c) s[c] = add_across<Q>(s[c]);
+                bits = 1;
+                if (!ROW || l >= 3) {
 #pragma unroll
-                for (int ct = 0; ct < CT; ++ct) {
-                    if (lev == 1) dst[16 * ct] = s[ct][0];
-                    else unsafeAtomicAdd(dst + 16 * ct, s[ct][0]);
+                    for (int c = 0; c < 4; ++c) s[c] = add_across<2 * Q>(s[c]);
+                    bits = 3;
+                }
+                if (NP == 8 && l >= (ROW ? 4 : 3)) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) s[c] = add_across<32>(s[c]);
+                    bits = 7;
                 }
             }
-            if (want_dw) {
-                float part[4] = {0.f, 0.f, 0.f, 0.f};
+            // (a group's first parent exists whenever any does)
+            if (l0 + j < L && pv && (i & bits) == 0) {
+                float* const dst = reinterpret_cast<float*>(reinterpret_cast<unsigned char*>(a.dm_out[l] + map[j]) + row[j]);
+                if (l == 1 || (ROW ? (1 << (l - 1)) <= NP : l == 2)) {      // uniform
+                    *reinterpret_cast<float4_t*>(dst) = s;
+                } else {
 #pragma unroll
-                for (int ct = 0; ct < CT; ++ct) {
-                    const auto hf = __builtin_amdgcn_permlane32_swap(__float_as_uint(mm[ct]), __float_as_uint(mm[ct]), false, false);
-                    const auto lo = __builtin_amdgcn_permlane16_swap(hf[0], hf[0], false, false);
-                    const auto hi = __builtin_amdgcn_permlane16_swap(hf[1], hf[1], false, false);
-                    part[0] += dv[ct] * __uint_as_float(lo[0]);
-                    part[1] += dv[ct] * __uint_as_float(lo[1]);
-                    part[2] += dv[ct] * __uint_as_float(hi[0]);
-                    part[3] += dv[ct] * __uint_as_float(hi[1]);
+                    for (int c = 0; c < 4; ++c) unsafeAtomicAdd(dst + c, s[c]);
                 }
+            }
+        }
+        if (want_dw) {
+            // lane e stores token e >> 1's levels l0 + 2 (e & 1) and the next
+            const int q = (e >> 1) & 3;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) part[j] = row_allreduce(part[j], [](float p, float q) { return p + q; });
-                const float mine = n16 == 0 ? part[0] : n16 == 1 ? part[1] : n16 == 2 ? part[2] : part[3];
-                if (n16 < 4 && l0 + n16 < L && qv) store_at<float>(a.dw + wq_off, (wrow + l0 + n16) * 4u, mine);
+            for (int j = 0; j < 4; ++j) {
+                const float v = q == 0 ? part[0][j] : q == 1 ? part[1][j] : q == 2 ? part[2][j] : part[3][j];
+                const uint32_t wr = q == 0 ? wrow[0] : q == 1 ? wrow[1] : q == 2 ? wrow[2] : wrow[3];
+                const bool on = q == 0 ? qv[0] : q == 1 ? qv[1] : q == 2 ? qv[2] : qv[3];
+                if (e < 8 && (e & 1) == (j >> 1) && l0 + j < L && on)
+                    store_at<float>(a.dw + (static_cast<size_t>(b) * N * a.heads + h) * L, (wr + l0 + j) * 4u, v);
             }
         }
     }
 }
 
 // ---------------------------------------------------------------------------------------------
-// key pass of the finest level
+// key pass
 // ---------------------------------------------------------------------------------------------
 
-// One chunk of one kept key J's parent list (up to kKeyChunk = 16 parents, NT = 1, 2 or 4 tiles of four):
-// slot s = 4e + child is a child of parent e, and vector g one of J's four children (the keys). Roles as in
-// the query pass with queries and keys exchanged: logits and <dout, v> from the gathered query and dout rows,
-// then dk = scale dx^T Q and dv = vw^T dout with the rows in LDS, the query rows first.
-template <int D, int NT, bool VA>
-__device__ __forceinline__ void key_chunk(const BwdLevelArgs& a, const int chunk, const int key, const int first, const int nch,
-                                          const int beg, const int nent, unsigned char* const base)
+// A kept key J and this head: its four children (the keys) as MFMA operands, row n16 holding key n16 >> 2 (rows
+// clamped onto the map).
+template <int D>
+struct KeyRows {
+    int bh, b, h, Jy, Jx;
+    bf16x8_t k[D / 32], v[D / 32];
+};
+
+template <int D, bool FINEST>
+__device__ __forceinline__ void key_rows(const BwdLevelArgs& a, const int key, KeyRows<D>& r)
+{
+    const int lane = threadIdx.x & 63, n16 = lane & 15, g = lane >> 4;
+    const int Np = a.Hp * a.Wp;
+    r.bh = fast_div(key, a.div_Np);
+    const int J = key - r.bh * Np;
+    r.b = fast_div(r.bh, a.div_heads);
+    r.h = r.bh - r.b * a.heads;
+    r.Jy = fast_div(J, a.div_Wp);
+    r.Jx = J - r.Jy * a.Wp;
+    const bool blocked = !FINEST && a.blocked;
+    const size_t map0 = blocked ? static_cast<size_t>(key) * 4 * D * 2
+                                : (static_cast<size_t>(r.b) * a.H * a.W * a.C + r.h * D) * 2;
+    const int c = n16 >> 2;
+    const uint32_t tok = static_cast<uint32_t>(__mul24(min(2 * r.Jy + (c >> 1), a.H - 1), a.W) + min(2 * r.Jx + (c & 1), a.W - 1));
+    // (a child off the map reads a clamped row, or in blocked storage the first child: its products are not used)
+    const bool on = 2 * r.Jy + (c >> 1) < a.H && 2 * r.Jx + (c & 1) < a.W;
+    const uint32_t roff = blocked ? static_cast<uint32_t>((on ? c : 0) * D * 2) : __umul24(tok, static_cast<uint32_t>(a.C * 2));
+#pragma unroll
+    for (int j = 0; j < D / 32; ++j) {
+        const uint32_t at = roff + static_cast<uint32_t>((g + 4 * j) * 16);
+        r.k[j] = __builtin_bit_cast(bf16x8_t, load_at<uint4>(static_cast<const unsigned char*>(a.k) + map0, at));
+        r.v[j] = __builtin_bit_cast(bf16x8_t, load_at<uint4>(static_cast<const unsigned char*>(a.v) + map0, at));
+    }
+}
+
+// Up to 16 of the parents that kept the key (entries beg .., NT = 1, 2 or 4 tiles of four): slot s = 4e + child
+// is a child of parent e, and vector g one of the four keys. Roles as in the query pass with queries and
+// keys exchanged: logits and <dout, v> from the gathered query and dout rows, then ok += dx^T Q and
+// ov += vw^T dout with the rows in LDS, the query rows first. At the coarser levels dm stands in dout's place,
+// fp32 rows as three bf16 terms (of the nine products of terms with vw's the three below 2^-26 are left out).
+template <int D, int NT, bool VA, bool FINEST>
+__device__ __forceinline__ void key_part(const BwdLevelArgs& a, const KeyRows<D>& kr, const int beg, const int nent,
+                                         unsigned char* const base, float4_t (&ok)[D / 16], float4_t (&ov)[D / 16])
 {
     constexpr int RB = D * 2;
     constexpr int NJ = RB / 64;
-    constexpr int CT = D / 16;
     constexpr int TS = tile_bytes<D>();
-    const int lane = threadIdx.x & 63, n16 = lane & 15, g = lane >> 4;
+    // (opaque: what follows from the lane is worked out again for each part rather than held in registers
+    // across the parts, for every number of tiles: 116 registers, and half the waves)
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    const int n16 = lane & 15, g = lane >> 4;
     lds_byte* const rows = (lds_byte*)base;
     lds_byte* const work = rows + NT * TS;
     const int Np = a.Hp * a.Wp;
-    const int bh = fast_div(key, a.div_Np), J = key - bh * Np;
-    const int b = fast_div(bh, a.div_heads), h = bh - b * a.heads;
+    const int bh = kr.bh, b = kr.b, h = kr.h, Jy = kr.Jy, Jx = kr.Jx;
     const int H = a.H, W = a.W, C = a.C, N = H * W, K = a.Kp;
-    const int Jy = fast_div(J, a.div_Wp), Jx = J - Jy * a.Wp;
     const uint32_t tok_bytes = static_cast<uint32_t>(C * 2);
-    const size_t map0 = (static_cast<size_t>(b) * N * C + h * D) * 2;
+    const size_t map0 = static_cast<size_t>(b) * N * C + h * D;           // elements
+    const bool blocked = !FINEST && a.blocked;
 
-    // ---- the slot this lane addresses: child (own & 3) of parent own >> 2 of the chunk (the children of a
+    // ---- the slot this lane addresses: child (own & 3) of parent own >> 2 of the part (the children of a
     //      parent on neighbouring quads), its row, its query's statistics and w_0 ----
     const int own = 16 * (lane & 3) + (lane >> 2);
-    const int ent = load_at<int32_t>(a.entries + beg, static_cast<uint32_t>(min(own >> 2, max(nent - 1, 0))) * 4u);
-    // the four keys: MFMA operand row n16 holds key n16 >> 2, rows clamped onto the map
-    bf16x8_t ka[NJ], va[NJ];
-    {
-        const int c = n16 >> 2;
-        const uint32_t tok = static_cast<uint32_t>(__mul24(min(2 * Jy + (c >> 1), H - 1), W) + min(2 * Jx + (c & 1), W - 1));
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const uint32_t at = __umul24(tok, tok_bytes) + static_cast<uint32_t>((g + 4 * j) * 16);
-            ka[j] = __builtin_bit_cast(bf16x8_t, load_at<uint4>(static_cast<const unsigned char*>(a.k) + map0, at));
-            va[j] = __builtin_bit_cast(bf16x8_t, load_at<uint4>(static_cast<const unsigned char*>(a.v) + map0, at));
-        }
-    }
-    const int Pc = nent > 0 ? ent : 0;
-    const int P = fast_div(Pc, a.div_Kp), r = Pc - P * K;
+    const int ent = load_at<int32_t>(a.entries + beg, static_cast<uint32_t>(min(own >> 2, nent - 1)) * 4u);
+    const int P = fast_div(ent, a.div_Kp), r = ent - P * K;
     const int Py = fast_div(P, a.div_Wp), Px = P - Py * a.Wp;
     const int qy = 2 * Py + ((own >> 1) & 1), qx = 2 * Px + (own & 1);
     const bool qv = (own >> 2) < nent && qy < H && qx < W;
     const uint32_t qtok = static_cast<uint32_t>(__mul24(min(qy, H - 1), W) + min(qx, W - 1));
     const uint64_t okm = __ballot(qv);                        // bit 4n + t: slot 16t + n holds a query
+    const uint32_t chunk = gather_chunk(lane);
     uint32_t off[NT];
-    quad_offsets<NT>(__umul24(qtok, tok_bytes), gather_chunk(lane), off);
-    const unsigned char* const dbase = static_cast<const unsigned char*>(a.dout) + map0;
-    const __amdgpu_buffer_rsrc_t qres = map_resource(static_cast<const unsigned char*>(a.q) + map0);
-    uint4 dc[NT][NJ];
+    // (a child off the map reads its parent's first: in blocked storage its own place is unwritten padding, and
+    // a row of weight 0 must still be finite)
+    const int child = qy < H && qx < W ? own & 3 : 0;
+    quad_offsets<NT>(blocked ? static_cast<uint32_t>((P * 4 + child) * RB) : __umul24(qtok, tok_bytes), chunk, off);
+    const __amdgpu_buffer_rsrc_t qres = map_resource(static_cast<const unsigned char*>(a.q) +
+        (blocked ? static_cast<size_t>(bh) * Np * 4 * RB : map0 * 2));
+    // this lane's chunk of each slot's dout row, or the eight floats of it of each dm row
+    uint4 dc[FINEST ? NT : 1][NJ];
+    float4_t dmf[FINEST ? 1 : NT][NJ][2];
+    if constexpr (FINEST) {
+        const unsigned char* const dbase = static_cast<const unsigned char*>(a.dout) + map0 * 2;
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) dc[t][j] = load_at<uint4>(dbase, off[t] + 64 * j);
+            for (int j = 0; j < NJ; ++j) dc[t][j] = load_at<uint4>(dbase, off[t] + 64 * j);
+    } else {
+        uint32_t moff[NT];
+        quad_offsets<NT>(qtok * static_cast<uint32_t>(C) * 4u, 2 * chunk, moff);
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) dmf[t][j][i] = load_at<float4_t>(a.dm + map0, moff[t] + 128 * j + 16 * i);
+    }
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
         for (int j = 0; j < NJ; ++j) load_lds16(qres, off[t], 64 * j, rows + t * TS + j * 1024);
     const float* const st_b = a.stats + static_cast<size_t>(bh) * static_cast<uint32_t>(N * 2 * (VA ? K : 1));
     const float2_t st = load_at<float2_t>(st_b, (VA ? qtok * static_cast<uint32_t>(K) + r : qtok) * 8u);
-    float scale_w = 1.0f;                                     // B: w_0 of the slot's query; A: the parent's score
-    if constexpr (VA) scale_w = a.parent_key[(static_cast<size_t>(bh) * Np + P) * K + r];
-    else scale_w = a.w ? load_at<float>(a.w + static_cast<size_t>(b) * static_cast<uint32_t>(N * a.heads * a.levels),
-                                        (qtok * static_cast<uint32_t>(a.heads) + h) * static_cast<uint32_t>(a.levels) * 4u)
-                       : 1.0f / a.levels;
+    float scale_w = 1.0f;                                     // level 0 of B: w_0 of the slot's query; A: the parent's score
+    if constexpr (VA) {
+        scale_w = a.parent_key[(static_cast<size_t>(bh) * Np + P) * K + r];
+    } else if constexpr (FINEST) {
+        scale_w = a.w ? load_at<float>(a.w + static_cast<size_t>(b) * static_cast<uint32_t>(N * a.heads * a.levels),
+                                       (qtok * static_cast<uint32_t>(a.heads) + h) * static_cast<uint32_t>(a.levels) * 4u)
+                      : 1.0f / a.levels;
+    }
+    // the p-th bf16 term of this lane's chunk of slot 16t + (lane >> 2)
+    auto term = [&](int t, int j, int p) -> uint4 {
+        if constexpr (FINEST) {
+            return dc[t][j];
+        } else {
+            uint32_t w[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const Split2 s = split2(dmf[t][j][i >> 1][2 * (i & 1)], dmf[t][j][i >> 1][2 * (i & 1) + 1]);
+                w[i] = p == 0 ? s.hi : p == 1 ? s.mid : s.lo;
+            }
+            return make_uint4(w[0], w[1], w[2], w[3]);
+        }
+    };
+    constexpr int DP = FINEST ? 1 : 3;
 
     // ---- <dout, v> and logits: lane 16g + n holds key g's of slots 16t + n ----
     float gs[NT], x[NT];
@@ -453,7 +666,9 @@ __device__ __forceinline__ void key_chunk(const BwdLevelArgs& a, const int chunk
         float4_t ag = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
-            ag = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[j], pass_operand(dc[t][j], work, lane), ag, 0, 0, 0);
+#pragma unroll
+            for (int p = 0; p < DP; ++p)
+                ag = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kr.v[j], pass_operand(term(t, j, p), work, lane), ag, 0, 0, 0);
         gs[t] = ag[0];
     }
     wait_lds_loads();                                         // the query rows
@@ -462,7 +677,7 @@ __device__ __forceinline__ void key_chunk(const BwdLevelArgs& a, const int chunk
         float4_t ax = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
-            ax = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[j], tile_operand(rows + t * TS + j * 1024, lane), ax, 0, 0, 0);
+            ax = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kr.k[j], tile_operand(rows + t * TS + j * 1024, lane), ax, 0, 0, 0);
         x[t] = ax[0];
     }
     const int ky = 2 * Jy + (g >> 1), kx = 2 * Jx + (g & 1);
@@ -474,30 +689,80 @@ __device__ __forceinline__ void key_chunk(const BwdLevelArgs& a, const int chunk
         const int src = 16 * n16 + 4 * t;
         const float lse = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(st[0])));
         const float Dq = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(st[1])));
-        const float sw = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(scale_w)));
         const bool valid = key_ok && ((okm >> (4 * n16 + t)) & 1ull) != 0ull;
         const float pr = valid ? __expf(x[t] * a.scale - lse) : 0.f;      // B: p; A: t
-        vw[t] = sw * pr;                                                  // B: w_0 p (the dout rows come without w_0); A: s
-        dx[t] = VA ? vw[t] * (gs[t] - Dq) : pr * (sw * gs[t] - Dq);
+        if constexpr (!VA && !FINEST) {
+            vw[t] = pr;
+            dx[t] = pr * (gs[t] - Dq);
+        } else {
+            const float sw = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(scale_w)));
+            vw[t] = sw * pr;                                  // B: w_0 p (the dout rows come without w_0); A: s
+            if constexpr (VA && !FINEST) {
+                // a key that the query keeps is refined at level l-1: its score's gradient comes from there, and
+                // it has no weight in this level's message
+                const int tok = ky * W + kx;
+                const size_t srow = (static_cast<size_t>(bh) * N + static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(src, static_cast<int>(qtok)))) * a.Ks;
+                bool kept = false;
+                float ds = gs[t];
+                for (int mm = 0; mm < a.Ks; ++mm) {
+                    if (valid && a.sel_idx[srow + mm] == tok) {
+                        kept = true;
+                        ds = a.dsig_in[srow + mm];
+                    }
+                }
+                dx[t] = vw[t] * (ds - Dq);
+                vw[t] = kept ? 0.f : vw[t];
+            } else {
+                dx[t] = VA ? vw[t] * (gs[t] - Dq) : pr * (sw * gs[t] - Dq);
+            }
+        }
     }
 
-    // ---- dk from the query rows, then dv from the dout rows in their place ----
-    float4_t ok[CT], ov[CT];
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) ok[ct] = ov[ct] = float4_t{0.f, 0.f, 0.f, 0.f};
+    // ---- dk from the query rows, then dv from the dout (dm) rows in their place ----
     store_split<NT>(work, dx, lane);
     wave_lds_sync();
     mma_rows<D, NT, 3>(ok, work, 128 * NT, rows, lane);
     wave_lds_sync();
     store_split<NT>(work, vw, lane);
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
+    for (int p = 0; p < DP; ++p) {
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
-            *(lds_ptr<u32x4_t>)(rows + t * TS + j * 1024 + lane * 16) = __builtin_bit_cast(u32x4_t, dc[t][j]);
-    wave_lds_sync();
-    mma_rows<D, NT, 3>(ov, work, 128 * NT, rows, lane);
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                *(lds_ptr<u32x4_t>)(rows + t * TS + j * 1024 + lane * 16) = __builtin_bit_cast(u32x4_t, term(t, j, p));
+        wave_lds_sync();
+        if (p == 0) mma_rows<D, NT, 3>(ov, work, 128 * NT, rows, lane);
+        else if (p == 1) mma_rows<D, NT, 2>(ov, work, 128 * NT, rows, lane);
+        else mma_rows<D, NT, 1>(ov, work, 128 * NT, rows, lane);
+        wave_lds_sync();                 // the rows are read before the next ones replace them
+    }
+}
 
+// One chunk of a kept key's list: up to kKeyGroup parents, 16 at a time, only the tiles that hold parents (lists
+// of a few are common). Longer chunks write fewer partial rows for bwd_key_reduce_kernel to add up, and spread
+// long lists over fewer waves: chunks of 16, 32 and 64 parents measured 421, 397 and 410 us a backward
+// (200x336, 2 x 32, K = 16, batch 2) and 200 to 201 (32 maps of 56x56, 1 x 64, K = 8).
+template <int D, bool VA, bool FINEST>
+__device__ __forceinline__ void key_chunk(const BwdLevelArgs& a, const int chunk, const int key, const int nch, int beg,
+                                          int left, unsigned char* const base)
+{
+    constexpr int CT = D / 16;
+    const int lane = threadIdx.x & 63, n16 = lane & 15, g = lane >> 4;
+    KeyRows<D> kr;
+    key_rows<D, FINEST>(a, key, kr);
+    float4_t ok[CT], ov[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) ok[ct] = ov[ct] = float4_t{0.f, 0.f, 0.f, 0.f};
+    while (left > 0) {                                        // uniform
+        const int nent = min(left, kKeyChunk);
+        if (nent > 8) key_part<D, 4, VA, FINEST>(a, kr, beg, nent, base, ok, ov);
+        else if (nent > 4) key_part<D, 2, VA, FINEST>(a, kr, beg, nent, base, ok, ov);
+        else key_part<D, 1, VA, FINEST>(a, kr, beg, nent, base, ok, ov);
+        beg += kKeyChunk;
+        left -= kKeyChunk;
+    }
+    const int ky = 2 * kr.Jy + (g >> 1), kx = 2 * kr.Jx + (g & 1);
     if (nch > 1) {
         // this chunk's rows; bwd_key_reduce_kernel adds up the key's chunks
         float* const pk = a.partial + ((static_cast<size_t>(chunk) * 4 + g) * 2) * D + n16;
@@ -506,14 +771,30 @@ __device__ __forceinline__ void key_chunk(const BwdLevelArgs& a, const int chunk
             pk[16 * ct] = ok[ct][0];
             pk[D + 16 * ct] = ov[ct][0];
         }
-    } else if (key_ok) {
-        const size_t row = (static_cast<size_t>(b) * N + ky * W + kx) * C + h * D + n16;
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-            a.dk[row + 16 * ct] = a.scale * ok[ct][0];
-            a.dv[row + 16 * ct] = ov[ct][0];
-        }
+        return;
     }
+    const bool on = ky < a.H && kx < a.W;
+    const size_t map0 = static_cast<size_t>(kr.b) * a.H * a.W * a.C + kr.h * D;
+    const uint32_t at = static_cast<uint32_t>((min(ky, a.H - 1) * a.W + min(kx, a.W - 1)) * a.C);
+    float rk[CT], rv[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+        rk[ct] = a.scale * ok[ct][0];
+        rv[ct] = ov[ct][0];
+    }
+    // J's own totals, level l+1's, go to its children in equal shares
+    const float share = child_share(kr.Jy, kr.Jx, a.H, a.W);
+    const size_t up = (static_cast<size_t>(kr.b) * a.Hp * a.Wp + kr.Jy * a.Wp + kr.Jx) * a.C + kr.h * D + n16;
+    if (a.up_k) {                                             // uniform
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) rk[ct] += share * a.up_k[up + 16 * ct];
+    }
+    if (a.up_v) {
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) rv[ct] += share * a.up_v[up + 16 * ct];
+    }
+    store_row<D, FINEST>(a.dk, FINEST && a.out_bf16, map0, at, rk, on, lane);
+    store_row<D, FINEST>(a.dv, FINEST && a.out_bf16, map0, at, rv, on, lane);
 }
 
 }  // namespace bwd16

@@ -803,12 +803,13 @@ size_t qta_backward_workspace_bytes_ex(int B, int heads, int H, int W, int d, in
 
 namespace {
 
-// The backward pass; with only_finest, just the level-0 kernel (for profiling it alone).
+// The backward pass; with only_finest, just the level-0 step (for profiling it alone). out16: NULL, or bf16 maps
+// that receive dq, dk, dv (dtype QTA_BF16, levels > 1); dq, dk, dv are then scratch.
 qta_status backward_impl(const void* q, const void* k, const void* v, const float* w, const void* dout, int B,
                          int heads, int H, int W, int d, int levels, int K, qta_variant variant, qta_dtype dtype,
                          float scale, const qta_options* opt, const void* workspace, size_t workspace_bytes,
                          float* dq, float* dk, float* dv, float* dw, void* bwd_workspace, size_t bwd_workspace_bytes,
-                         void* stream, bool only_finest)
+                         void* stream, bool only_finest, void* const* out16)
 {
     qta_status st = check_problem(B, heads, d, 1, variant, dtype);
     if (st != QTA_OK) return st;
@@ -894,103 +895,71 @@ qta_status backward_impl(const void* q, const void* k, const void* v, const floa
     const int c = levels - 1;
     if (only_finest && levels < 2) return QTA_ERR_INVALID;
 
-    if (levels > 1 && !only_finest) {
-        // clear what is accumulated: dm of levels >= 2 and the kept-by counts
-        FillRange r[1];
-        r[0] = FillRange{fptr(G.zero_begin), (G.zero_end - G.zero_begin) / sizeof(float)};
-        if (launch_fill_zero(r, 1, s) != hipSuccess) return QTA_ERR_HIP;
-
-
-    }
-    if (levels > 1) {
-        // 2. finer levels, finest first (QuadTree-A's score gradients go up one level each)
-        for (int l = 0; l < (only_finest ? 1 : c); ++l) {
-            // with an auxiliary stream the finest level's sort and key pass (the largest) go there
-            // right after its query pass. The coarser levels' sorts and key passes go to the third
-            // stream when there is one, each right after its level's query pass; with two streams
-            // only, when the coarse level's tile kernels leave compute units idle (fewer 16-row
-            // tiles than units) they follow those on the caller's stream, so that the coarse level
-            // runs beside the finest key pass, and otherwise they go to the auxiliary stream too
-            BwdLevelArgs a{};
-            if (l == 0) {
-                a.q = q;
-                a.k = k;
-                a.v = v;
-                a.blocked = false;
-                a.dout = dout;
-                a.w = va ? nullptr : w;
-                a.dq = dq;
-                a.dk = dk;
-                a.dv = dv;
-                a.dw = dw_out;
-                for (int j = 1; j < levels; ++j) {      // 1. the combination's backward
-                    a.dm_out[j] = fptr(G.dm[j]);
-                    a.msg_fwd[j] = reinterpret_cast<const float*>(ws + L.msg[j]);
-                    a.lvl_W[j] = L.W[j];
-                    a.lvl_N[j] = L.H[j] * L.W[j];
-                }
-            } else {
-                a.q = ws + L.q[l];
-                a.k = ws + L.k[l];
-                a.v = vlev(l);
-                a.blocked = L.blocked[l] != 0;
-                a.sel_idx = sidx(l);
-                a.dsig_in = va ? fptr(G.dsig[l]) : nullptr;
-                a.dm = fptr(G.dm[l]);
-                a.dq = fptr(G.gq[l]);
-                a.dk = fptr(G.gk[l]);
-                a.dv = gvlev(l);
+    // the arguments of finer level l and of its counting sort
+    auto level_args = [&](int l, BwdScanArgs* sc) -> BwdLevelArgs {
+        BwdLevelArgs a{};
+        if (l == 0) {
+            a.q = q;
+            a.k = k;
+            a.v = v;
+            a.blocked = false;
+            a.dout = dout;
+            a.w = va ? nullptr : w;
+            a.dq = dq;
+            a.dk = dk;
+            a.dv = dv;
+            a.dw = dw_out;
+            for (int j = 1; j < levels; ++j) {      // 1. the combination's backward
+                a.dm_out[j] = fptr(G.dm[j]);
+                a.msg_fwd[j] = reinterpret_cast<const float*>(ws + L.msg[j]);
+                a.lvl_W[j] = L.W[j];
+                a.lvl_N[j] = L.H[j] * L.W[j];
             }
-            a.B = B;
-            a.heads = heads;
-            a.H = L.H[l];
-            a.W = L.W[l];
-            a.Hp = L.H[l + 1];
-            a.Wp = L.W[l + 1];
-            a.C = C;
-            a.Kp = Kl[l + 1];
-            a.Ks = l >= 1 ? Kl[l] : 0;
-            a.scale = tau;
-            a.parent_idx = sidx(l + 1);
-            a.parent_key = skey(l + 1);
-            a.dsig_out = va ? fptr(G.dsig[l + 1]) : nullptr;
-            a.levels = levels;
-            a.stats = fptr(G.qstats[l]);
-            a.count = reinterpret_cast<int32_t*>(gws + G.count[l]);
-            a.off = reinterpret_cast<const int32_t*>(gws + G.off[l]);
-            a.coff = reinterpret_cast<const int32_t*>(gws + G.coff[l]);
-            a.chunk_key = reinterpret_cast<const int32_t*>(gws + G.chunk_key[l]);
-            a.entries = reinterpret_cast<int32_t*>(gws + G.entries[l]);
-            a.slot = reinterpret_cast<int32_t*>(gws + G.slot[l]);
-            a.partial = fptr(G.partial[l]);
-            // QuadTree-B with three streams and one intermediate level (`qside`): that level's query
-            // pass needs only the finest query pass (every dm comes from it), so it runs on the
-            // third stream beside the coarse level
-            const hipStream_t sq = (l > 0 && qside) ? s3 : s;
-            if (launch_bwd_level(a, d, va, use_bf16, l == 0, sq) != hipSuccess) return QTA_ERR_HIP;
-            if (l == 0 && qside && !after(s, s3)) return QTA_ERR_HIP;
-            // the stream of this level's sort and key pass, which need its query pass
-            const hipStream_t sk = l == 0 ? s2 : (s3 != s ? s3 : (defer_coarser ? s : s2));
-            if (sk != sq && !after(sq, sk)) return QTA_ERR_HIP;
-            BwdScanArgs sc{};
-            sc.n = B * heads * L.H[l + 1] * L.W[l + 1];
-            sc.nblocks = (sc.n + 1023) / 1024;
-            sc.count = a.count;
-            sc.off = reinterpret_cast<int32_t*>(gws + G.off[l]);
-            sc.coff = reinterpret_cast<int32_t*>(gws + G.coff[l]);
-            sc.chunk_key = reinterpret_cast<int32_t*>(gws + G.chunk_key[l]);
-            sc.block_sums = reinterpret_cast<int32_t*>(gws + G.block_sums[l]);
-            if (s2 != s && l > 0 && defer_coarser) {
-                deferred[ndeferred++] = DeferredKeys{a, sc, l};
-                continue;
-            }
-            if (launch_bwd_keys(a, sc, d, va, use_bf16, l == 0, sk) != hipSuccess) return QTA_ERR_HIP;
+        } else {
+            a.q = ws + L.q[l];
+            a.k = ws + L.k[l];
+            a.v = vlev(l);
+            a.blocked = L.blocked[l] != 0;
+            a.sel_idx = sidx(l);
+            a.dsig_in = va ? fptr(G.dsig[l]) : nullptr;
+            a.dm = fptr(G.dm[l]);
+            a.dq = fptr(G.gq[l]);
+            a.dk = fptr(G.gk[l]);
+            a.dv = gvlev(l);
         }
-    }
-    if (only_finest) return QTA_OK;
-
-    // 3. coarsest level
-    {
+        a.B = B;
+        a.heads = heads;
+        a.H = L.H[l];
+        a.W = L.W[l];
+        a.Hp = L.H[l + 1];
+        a.Wp = L.W[l + 1];
+        a.C = C;
+        a.Kp = Kl[l + 1];
+        a.Ks = l >= 1 ? Kl[l] : 0;
+        a.scale = tau;
+        a.parent_idx = sidx(l + 1);
+        a.parent_key = skey(l + 1);
+        a.dsig_out = va ? fptr(G.dsig[l + 1]) : nullptr;
+        a.levels = levels;
+        a.stats = fptr(G.qstats[l]);
+        a.count = reinterpret_cast<int32_t*>(gws + G.count[l]);
+        a.off = reinterpret_cast<const int32_t*>(gws + G.off[l]);
+        a.coff = reinterpret_cast<const int32_t*>(gws + G.coff[l]);
+        a.chunk_key = reinterpret_cast<const int32_t*>(gws + G.chunk_key[l]);
+        a.entries = reinterpret_cast<int32_t*>(gws + G.entries[l]);
+        a.slot = reinterpret_cast<int32_t*>(gws + G.slot[l]);
+        a.partial = fptr(G.partial[l]);
+        *sc = BwdScanArgs{};
+        sc->n = B * heads * L.H[l + 1] * L.W[l + 1];
+        sc->nblocks = (sc->n + 1023) / 1024;
+        sc->count = a.count;
+        sc->off = reinterpret_cast<int32_t*>(gws + G.off[l]);
+        sc->coff = reinterpret_cast<int32_t*>(gws + G.coff[l]);
+        sc->chunk_key = reinterpret_cast<int32_t*>(gws + G.chunk_key[l]);
+        sc->block_sums = reinterpret_cast<int32_t*>(gws + G.block_sums[l]);
+        return a;
+    };
+    auto coarse_args = [&]() -> BwdCoarseArgs {
         BwdCoarseArgs a{};
         a.B = B;
         a.heads = heads;
@@ -1022,7 +991,89 @@ qta_status backward_impl(const void* q, const void* k, const void* v, const floa
             a.dk = fptr(G.gk[c]);
             a.dv = gvlev(c);
         }
-        if (launch_bwd_coarse(a, d, va, use_bf16, s) != hipSuccess) return QTA_ERR_HIP;
+        return a;
+    };
+
+    if (levels > 1 && !only_finest) {
+        // clear what is accumulated: dm of levels >= 2 and the kept-by counts
+        FillRange r[1];
+        r[0] = FillRange{fptr(G.zero_begin), (G.zero_end - G.zero_begin) / sizeof(float)};
+        if (launch_fill_zero(r, 1, s) != hipSuccess) return QTA_ERR_HIP;
+    }
+    BwdScanArgs sc0{};
+    if (levels > 1 && launch_bwd_combine(level_args(0, &sc0), d, va, use_bf16, s) != hipSuccess) return QTA_ERR_HIP;
+
+    // a level's counting sort and key pass
+    auto keys = [&](const BwdLevelArgs& a, const BwdScanArgs& sc, bool finest, hipStream_t x) {
+        return launch_bwd_sort(a, sc, use_bf16, x) == hipSuccess &&
+               launch_bwd_keys(a, d, va, use_bf16, finest, x) == hipSuccess;
+    };
+
+    // QuadTree-B with bf16 inputs, coarse to fine: every message gradient comes from the combination, so no
+    // level waits for a finer one, and each level's passes add the level above's totals as they write (its
+    // queries and keys are the children of that level's tokens): no pass over the finished gradients
+    // afterwards, and the results go out in their final type. All of it runs on the caller's stream: side by
+    // side the passes only share the chip, and a hand-over between streams costs 10 to 15 us of the host's
+    // time (a key pass beside each finer query pass: 423 us a backward of 200x336 maps, 2 x 32, K = 16,
+    // batch 2, level 1's alone 420, on one stream 422; 32 maps of 56x56, 1 x 64, K = 8: 226, 209, 207).
+    // (QuadTree-A's score gradients go from fine to coarse, and the position encoding adds to every level's
+    // finished v gradients: those run finest first, below, as do fp32 inputs.)
+    if (use_bf16 && !va && !pe && levels > 1 && !only_finest) {
+        const BwdCoarseArgs ca = coarse_args();
+        if (launch_bwd_coarse(ca, d, va, use_bf16, false, s) != hipSuccess) return QTA_ERR_HIP;
+        if (launch_bwd_coarse(ca, d, va, use_bf16, true, s) != hipSuccess) return QTA_ERR_HIP;
+        for (int l = c - 1; l >= 0; --l) {
+            BwdScanArgs sc;
+            BwdLevelArgs a = level_args(l, &sc);
+            a.up_q = fptr(G.gq[l + 1]);
+            a.up_k = fptr(G.gk[l + 1]);
+            a.up_v = v_supplied ? nullptr : fptr(G.gv[l + 1]);
+            if (l == 0 && out16) {
+                a.out_bf16 = true;
+                a.dq = static_cast<float*>(out16[0]);
+                a.dk = static_cast<float*>(out16[1]);
+                a.dv = static_cast<float*>(out16[2]);
+            }
+            if (launch_bwd_level(a, d, va, use_bf16, l == 0, s) != hipSuccess) return QTA_ERR_HIP;
+            if (!keys(a, sc, l == 0, s)) return QTA_ERR_HIP;
+        }
+        return QTA_OK;
+    }
+
+    if (levels > 1) {
+        // 2. finer levels, finest first (QuadTree-A's score gradients go up one level each)
+        for (int l = 0; l < (only_finest ? 1 : c); ++l) {
+            // with an auxiliary stream the finest level's sort and key pass (the largest) go there
+            // right after its query pass. The coarser levels' sorts and key passes go to the third
+            // stream when there is one, each right after its level's query pass; with two streams
+            // only, when the coarse level's tile kernels leave compute units idle (fewer 16-row
+            // tiles than units) they follow those on the caller's stream, so that the coarse level
+            // runs beside the finest key pass, and otherwise they go to the auxiliary stream too
+            BwdScanArgs sc;
+            const BwdLevelArgs a = level_args(l, &sc);
+            // QuadTree-B with three streams and one intermediate level (`qside`): that level's query
+            // pass needs only the finest query pass (every dm comes from it), so it runs on the
+            // third stream beside the coarse level
+            const hipStream_t sq = (l > 0 && qside) ? s3 : s;
+            if (launch_bwd_level(a, d, va, use_bf16, l == 0, sq) != hipSuccess) return QTA_ERR_HIP;
+            if (l == 0 && qside && !after(s, s3)) return QTA_ERR_HIP;
+            // the stream of this level's sort and key pass, which need its query pass
+            const hipStream_t sk = l == 0 ? s2 : (s3 != s ? s3 : (defer_coarser ? s : s2));
+            if (sk != sq && !after(sq, sk)) return QTA_ERR_HIP;
+            if (s2 != s && l > 0 && defer_coarser) {
+                deferred[ndeferred++] = DeferredKeys{a, sc, l};
+                continue;
+            }
+            if (!keys(a, sc, l == 0, sk)) return QTA_ERR_HIP;
+        }
+    }
+    if (only_finest) return QTA_OK;
+
+    // 3. coarsest level
+    {
+        const BwdCoarseArgs a = coarse_args();
+        if (launch_bwd_coarse(a, d, va, use_bf16, false, s) != hipSuccess) return QTA_ERR_HIP;
+        if (launch_bwd_coarse(a, d, va, use_bf16, true, s) != hipSuccess) return QTA_ERR_HIP;
     }
     // the position encoding's backward (every level, once all of the level's v gradients are
     // written; before the unpooling, which reads them)
@@ -1054,7 +1105,7 @@ qta_status backward_impl(const void* q, const void* k, const void* v, const floa
     };
     if (levels == 1) return (pe && posenc_bwd() != hipSuccess) ? QTA_ERR_HIP : QTA_OK;
     for (int i = 0; i < ndeferred; ++i)
-        if (launch_bwd_keys(deferred[i].a, deferred[i].sc, d, va, use_bf16, false, s) != hipSuccess) return QTA_ERR_HIP;
+        if (!keys(deferred[i].a, deferred[i].sc, false, s)) return QTA_ERR_HIP;
     if (s2 != s && !after(s2, s)) return QTA_ERR_HIP;       // the key passes before the unpooling
     if (s3 != s && !after(s3, s)) return QTA_ERR_HIP;
     if (pe && posenc_bwd() != hipSuccess) return QTA_ERR_HIP;
@@ -1077,6 +1128,7 @@ qta_status backward_impl(const void* q, const void* k, const void* v, const floa
     u.dq = dq;
     u.dk = dk;
     u.dv = dv;
+    for (int i = 0; i < 3; ++i) u.out16[i] = out16 ? out16[i] : nullptr;
     return launch_bwd_unpool(u, s) == hipSuccess ? QTA_OK : QTA_ERR_HIP;
 }
 
@@ -1091,7 +1143,7 @@ qta_status qta_backward_ex(const void* q, const void* k, const void* v, const fl
                            size_t bwd_workspace_bytes, void* stream)
 {
     return backward_impl(q, k, v, w, dout, B, heads, H, W, d, levels, K, variant, dtype, scale, opt, workspace,
-                         workspace_bytes, dq, dk, dv, dw, bwd_workspace, bwd_workspace_bytes, stream, false);
+                         workspace_bytes, dq, dk, dv, dw, bwd_workspace, bwd_workspace_bytes, stream, false, nullptr);
 }
 
 qta_status qta_backward_finest_ex(const void* q, const void* k, const void* v, const float* w, const void* dout,
@@ -1101,7 +1153,20 @@ qta_status qta_backward_finest_ex(const void* q, const void* k, const void* v, c
                                   void* bwd_workspace, size_t bwd_workspace_bytes, void* stream)
 {
     return backward_impl(q, k, v, w, dout, B, heads, H, W, d, levels, K, variant, dtype, scale, opt, workspace,
-                         workspace_bytes, dq, dk, dv, dw, bwd_workspace, bwd_workspace_bytes, stream, true);
+                         workspace_bytes, dq, dk, dv, dw, bwd_workspace, bwd_workspace_bytes, stream, true, nullptr);
+}
+
+qta_status qta_backward_bf16_ex(const void* q, const void* k, const void* v, const float* w, const void* dout, int B,
+                                int heads, int H, int W, int d, int levels, int K, qta_variant variant, float scale,
+                                const qta_options* opt, const void* workspace, size_t workspace_bytes, void* dq16,
+                                void* dk16, void* dv16, float* dq, float* dk, float* dv, float* dw, void* bwd_workspace,
+                                size_t bwd_workspace_bytes, void* stream)
+{
+    if (!dq16 || !dk16 || !dv16 || !aligned16(dq16) || !aligned16(dk16) || !aligned16(dv16)) return QTA_ERR_INVALID;
+    if (levels == 1) return QTA_ERR_UNSUPPORTED;
+    void* const out16[3] = {dq16, dk16, dv16};
+    return backward_impl(q, k, v, w, dout, B, heads, H, W, d, levels, K, variant, QTA_BF16, scale, opt, workspace,
+                         workspace_bytes, dq, dk, dv, dw, bwd_workspace, bwd_workspace_bytes, stream, false, out16);
 }
 
 }  // extern "C"

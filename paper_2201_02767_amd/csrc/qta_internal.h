@@ -268,6 +268,7 @@ inline long long posenc_bwd_blocks(int B, const int* Hl, const int* Wl, int leve
 // (parent, rank) pairs sorted by key, then one wave per chunk of one key's list: dk and dv of the
 // key's four children at level l, each row written once.
 constexpr int kKeyChunk = 16;       // parents per key-pass chunk
+constexpr int kKeyGroup = 32;       // the same in the bf16 key pass, which takes 16 at a time
 
 struct BwdLevelArgs {
     const void* q;
@@ -288,9 +289,15 @@ struct BwdLevelArgs {
     const void* dout;           // l == 0: upstream gradient, storage type [B][N][C]
     const float* w;             // l == 0, QuadTree-B: [B][N][heads][L] or NULL (1/L)
     int levels;
-    float* dq;                  // fp32 [B][N][C], written
+    float* dq;                  // fp32 [B][N][C], written (out_bf16: bf16 values instead)
     float* dk;                  // fp32 [B][N][C], written by the key pass
     float* dv;
+    bool out_bf16;              // l == 0 with bf16 inputs: dq, dk, dv point at bf16 [B][N][C]
+    // bf16 inputs: the gradients of level l+1's q, k and v with all its ancestors' added (fp32 [B][Np][C]), whose
+    // share each child receives here; NULL: not added (bwd_unpool_kernel does that)
+    const float* up_q;
+    const float* up_k;
+    const float* up_v;
     float* dw;                  // l == 0, QuadTree-B with w: entry 0 written; or NULL
     float* stats;               // B: [B][heads][N][2] (log-sum-exp, sum p ds); A: [B][heads][N][Kp][2]
     int32_t* count;             // [B*heads*Np] parents that kept each key (zero before the query pass;
@@ -311,11 +318,12 @@ struct BwdLevelArgs {
 // Scans of the kept-by counts of one level (n = B*heads*Np key slots, blocks of 1024).
 struct BwdScanArgs {
     int n, nblocks;
+    int chunk;                  // parents per key-pass chunk; set by launch_bwd_sort
     int32_t* count;
     int32_t* off;
     int32_t* coff;
     int32_t* chunk_key;
-    int32_t* block_sums;        // [2 * nblocks]
+    int32_t* block_sums;        // [2 * nblocks]: each block's counts and chunks
 };
 
 struct BwdFillArgs {
@@ -348,6 +356,13 @@ struct BwdCoarseArgs {
     float* dw;                  // single level, QuadTree-B with w
 };
 
+// The share of a level-(l+1) token's gradient that each of its valid children at level l receives: 1/n.
+__device__ __forceinline__ float child_share(int Py, int Px, int H, int W)
+{
+    const float fy = 2 * Py + 1 < H ? 0.5f : 1.0f, fx = 2 * Px + 1 < W ? 0.5f : 1.0f;
+    return fy * fx;
+}
+
 // Adds to the level-0 gradients every coarser level's, split evenly among valid children.
 struct BwdUnpoolArgs {
     int v_pooled;               // 0: V's coarser levels were given (their gradients stay there)
@@ -361,6 +376,7 @@ struct BwdUnpoolArgs {
     float* dq;
     float* dk;
     float* dv;
+    void* out16[3];             // bf16 maps that receive the results in place of dq, dk, dv; NULL: in place
 };
 
 struct FillRange {
@@ -429,14 +445,19 @@ hipError_t launch_topk(const TopkArgs& a, hipStream_t stream);
 // index ascending), empty slots (index -1) last.
 hipError_t launch_sort_rows(int32_t* idx, float* key, long long rows, int K, hipStream_t stream);
 hipError_t launch_fill_zero(const FillRange* r, int n, hipStream_t stream);
+// The combination's backward (a: level 0's arguments). With fp32 inputs the finest query pass does it.
+hipError_t launch_bwd_combine(const BwdLevelArgs& a, int d, bool variant_a, bool use_bf16, hipStream_t stream);
 hipError_t launch_bwd_level(const BwdLevelArgs& a, int d, bool variant_a, bool use_bf16, bool finest,
                             hipStream_t stream);
-// The bf16 forms behind launch_bwd_level and launch_bwd_keys (divisors set).
+// The bf16 forms behind launch_bwd_combine, launch_bwd_level and launch_bwd_keys (divisors set).
 hipError_t launch_bwd_query_bf16(const BwdLevelArgs& a, int d, bool variant_a, bool finest, hipStream_t stream);
-hipError_t launch_bwd_key_finest_bf16(const BwdLevelArgs& a, int d, bool variant_a, long long max_chunks, hipStream_t stream);
-hipError_t launch_bwd_keys(const BwdLevelArgs& a, const BwdScanArgs& sc, int d, bool variant_a, bool use_bf16,
-                           bool finest, hipStream_t stream);
-hipError_t launch_bwd_coarse(const BwdCoarseArgs& a, int d, bool variant_a, bool use_bf16, hipStream_t stream);
+hipError_t launch_bwd_combine_bf16(const BwdLevelArgs& a, int d, bool variant_a, hipStream_t stream);
+hipError_t launch_bwd_key_bf16(const BwdLevelArgs& a, int d, bool variant_a, bool finest, long long max_chunks, hipStream_t stream);
+// The counting sort of a level's kept pairs by key, after its query pass; then its key pass.
+hipError_t launch_bwd_sort(const BwdLevelArgs& a, const BwdScanArgs& sc, bool use_bf16, hipStream_t stream);
+hipError_t launch_bwd_keys(const BwdLevelArgs& a, int d, bool variant_a, bool use_bf16, bool finest, hipStream_t stream);
+// keys: the key pass (after the query pass of the same level), else the query pass.
+hipError_t launch_bwd_coarse(const BwdCoarseArgs& a, int d, bool variant_a, bool use_bf16, bool keys, hipStream_t stream);
 hipError_t launch_bwd_unpool(const BwdUnpoolArgs& a, hipStream_t stream);
 
 }  // namespace qta

@@ -77,6 +77,8 @@ _SIGS = {
     "qta_backward_workspace_bytes_ex": ([_I, _I, _I, _I, _I, _I, _I, _I, _I, _P], ctypes.c_size_t),
     "qta_backward_ex": ([_P, _P, _P, _P, _P, _I, _I, _I, _I, _I, _I, _I, _I, _I, _F, _P, _P, ctypes.c_size_t,
                          _P, _P, _P, _P, _P, ctypes.c_size_t, _P], _I),
+    "qta_backward_bf16_ex": ([_P, _P, _P, _P, _P, _I, _I, _I, _I, _I, _I, _I, _I, _F, _P, _P, ctypes.c_size_t,
+                              _P, _P, _P, _P, _P, _P, _P, _P, ctypes.c_size_t, _P], _I),
     "qta_backward_finest_ex": ([_P, _P, _P, _P, _P, _I, _I, _I, _I, _I, _I, _I, _I, _I, _F, _P, _P, ctypes.c_size_t,
                                 _P, _P, _P, _P, _P, ctypes.c_size_t, _P], _I),
     "qta_build_pyramid": ([_P, _P, _I, _I, _I, _I, _I, _I, _P], _I),
@@ -431,11 +433,22 @@ class Plan:
         ``dpe_bias`` and ``dv_levels`` (entry l >= 1). The returned tensors are the plan's own
         buffers, overwritten by the next call. ``overlap``: run the finest level's sort and key pass
         on a second stream and the coarser levels' on a third (both one per device for the process),
-        beside the query passes and the coarse level (False: everything on the one stream)."""
+        beside the query passes and the coarse level (False: everything on the one stream; QuadTree-B on
+        bf16 without an encoding always runs on the one)."""
         s = _stream(self.device) if stream is None else ctypes.c_void_p(stream)
         args, opt, grads = self._bwd_args(q, k, v, w, dout, s, overlap, v_levels, pe_weight, pe_bias)
         _check("qta_backward_ex", lib().qta_backward_ex(*args))
         return grads
+
+    def _backward_bf16(self, q, k, v, dout, w):
+        """The backward of a bf16 plan of several levels with dq, dk, dv rounded to bf16 in new tensors (the
+        same values as ``backward``'s cast to bf16, without the pass over fp32 ones); dw as in ``backward``."""
+        args, opt, (_, _, _, dw) = self._bwd_args(q, k, v, w, dout, _stream(self.device))
+        outs = [torch.empty_like(q) for _ in range(3)]
+        # (the arguments of qta_backward_ex without the dtype, and with the bf16 outputs before the fp32 ones)
+        _check("qta_backward_bf16_ex", lib().qta_backward_bf16_ex(
+            *args[:13], *args[14:18], *[_ptr(t) for t in outs], *args[18:]))
+        return (*outs, dw)
 
     def prepare_backward(self, q, k, v, dout, w=None, finest_only=False, v_levels=None, pe_weight=None, pe_bias=None):
         """Validate once and return a zero-argument callable that re-issues this backward on the
@@ -542,7 +555,11 @@ class _QuadTreeAttention(torch.autograd.Function):
         saved = ctx.saved_tensors
         q, k, v = saved[:3]
         w = saved[3] if len(saved) > 3 else None
-        dq, dk, dv, dw = ctx.plan.backward(q, k, v, dout.to(q.dtype).contiguous(), w)
+        dout = dout.to(q.dtype).contiguous()
+        if q.dtype == torch.bfloat16 and ctx.plan.levels > 1:
+            dq, dk, dv, dw = ctx.plan._backward_bf16(q, k, v, dout, w)
+            return dq, dk, dv, (dw.clone() if dw is not None else None), None
+        dq, dk, dv, dw = ctx.plan.backward(q, k, v, dout, w)
         cast = lambda t: None if t is None else t.to(q.dtype)
         return cast(dq), cast(dk), cast(dv), (dw.clone() if dw is not None else None), None
 

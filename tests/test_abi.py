@@ -336,6 +336,15 @@ def test_backward_validation():
     assert bwd(gwsb=need_a - 1) == WORKSPACE
     assert lib.qta_backward_workspace_bytes_ex(1, 1, 16, 16, 32, 3, 4, 7, F32, None) == 0
 
+    # the form with bf16 gradients: its outputs, and at least two levels
+    def bwd16(L=3, out=FAKE, gwsb=1 << 40):
+        return lib.qta_backward_bf16_ex(FAKE, FAKE, FAKE, None, FAKE, 1, 1, 16, 16, 32, L, 4, VB, 0.0, None, FAKE, 1 << 40,
+                                        FAKE, out, FAKE, FAKE, FAKE, FAKE, None, FAKE, gwsb, None)
+    assert bwd16(out=None) == INVALID
+    assert bwd16(out=FAKE + 8) == INVALID
+    assert bwd16(L=1) == UNSUPPORTED
+    assert bwd16(gwsb=0) == WORKSPACE
+
 
 def test_binding_structs_match_the_header(tmp_path):
     """The ctypes mirrors of the header's structs have the C layout: size and every field's offset,

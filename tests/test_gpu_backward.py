@@ -307,3 +307,29 @@ def test_autograd_function(dev):
     assert grad_err(to_np(k.grad.float()), to_np(dk)) <= 1e-2
     assert grad_err(to_np(v.grad.float()), to_np(dv)) <= 1e-2
     assert torch.equal(w.grad, dw)
+
+
+@pytest.mark.parametrize("variant", ["A", "B"])
+@pytest.mark.parametrize("B,H,W,heads,d,L,epipolar", [
+    (1, 19, 22, 2, 32, 3, False),
+    (2, 27, 33, 1, 64, 4, False),      # odd at every level: 1, 2 or 4 children
+    (1, 3, 45, 2, 32, 4, True),        # one-row maps
+    (1, 21, 20, 1, 32, 2, False),      # no intermediate level
+])
+def test_autograd_bf16_gradients_are_the_backwards_rounded(dev, variant, B, H, W, heads, d, L, epipolar):
+    """attention() on bf16 writes dq, dk, dv in bf16 straight from the backward: the values of Plan.backward
+    rounded once. Sums ordered by atomics may change the fp32 values' last bits, and so a rounding: one bf16
+    step (2^-7 of the value, and 1e-6 of the largest for sums that cancel) is allowed, to fewer than 1%."""
+    q, k, v, g = (torch.from_numpy(rand(800 + i, (B, H, W, heads, d), "bf16")).to(dev).bfloat16() for i in range(4))
+    w = torch.rand(B, H * W, heads, L, device=dev) if variant == "B" else None
+    plan = P.Plan(B, H, W, heads, d, levels=L, K=5, variant=variant, dtype=torch.bfloat16, device=dev, epipolar=epipolar)
+    plan.run(q, k, v, w)
+    ref = [t.clone() for t in plan.backward(q, k, v, g, w)[:3]]
+    leaves = [t.clone().requires_grad_(True) for t in (q, k, v)]
+    out = P.attention(*leaves, levels=L, K=5, variant=variant, w=w, plan=plan, epipolar=epipolar)
+    got = torch.autograd.grad(out, leaves, g)
+    for a, r in zip(got, ref):
+        assert a.dtype == torch.bfloat16 and a.shape == r.shape
+        diff = (a.float() - r).abs()
+        assert bool((diff <= r.abs() * 2.0 ** -7 + 1e-6 * r.abs().max()).all())
+        assert float((a != r.bfloat16()).float().mean()) < 1e-2
