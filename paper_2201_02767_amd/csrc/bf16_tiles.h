@@ -39,6 +39,23 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));
 }
 
+// x split into three bf16 terms: x = hi + mid + lo exactly (24 significant bits), two values a word.
+struct Split2 {
+    uint32_t hi, mid, lo;
+};
+__device__ __forceinline__ float low_half(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float high_half(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
+__device__ __forceinline__ Split2 split2(float x, float y)
+{
+    Split2 s;
+    s.hi = pack2(x, y);
+    x -= low_half(s.hi);
+    y -= high_half(s.hi);
+    s.mid = pack2(x, y);
+    s.lo = pack2(x - low_half(s.mid), y - high_half(s.mid));
+    return s;
+}
+
 // The value that lane T of each lane quad holds, in all four lanes.
 template <int T>
 __device__ __forceinline__ uint32_t quad_broadcast(uint32_t x)
@@ -120,6 +137,24 @@ __device__ __forceinline__ void store_weights(lds_byte* w, const float (&x)[NT],
         for (int t = 0; t < NT; t += 4)
             *(lds_ptr<u32x2_t>)(p + t * 2) = u32x2_t{pack2(x[t], x[t + 1]), pack2(x[t + 2], x[t + 3])};
     }
+}
+
+// Four tiles (64 slots) read transposed: channel tile ct of the eight slots of lane group g at step u (0 or 1),
+// n = g + 4 (2u + r), t = 0 .. 3 for r = 0, 1 (see mma_rows), as an MFMA operand.
+template <int D>
+__device__ __forceinline__ bf16x8_t rows_transposed4(lds_byte* rows, int u, int ct, int lane)
+{
+    constexpr int TS = tile_bytes<D>();
+    const int n16 = lane & 15, g = lane >> 4, k = n16 >> 2, c2 = (n16 >> 1) & 1;
+    lds_byte* const r0 = rows + k * TS + g * 64 + (n16 & 1) * 8;
+    short4_t v[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int x = 2 * u + r;
+        v[r] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            reinterpret_cast<lds_ptr<short4_t>>(r0 + ((c2 ^ x ^ (2 * (ct & 1))) * 16) + (ct >> 1) * 1024 + 256 * x));
+    }
+    return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(v[0], v[1], 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
 // acc[ct] += weights x rows on the 16x16 MFMA, contracted over the 16 NT slots: operand rows 4g .. 4g+3 are

@@ -24,23 +24,6 @@ namespace bwd16 {
 
 using namespace tiles;
 
-// x split into three bf16 terms: x = hi + mid + lo exactly (24 significant bits), two values a word.
-struct Split2 {
-    uint32_t hi, mid, lo;
-};
-__device__ __forceinline__ float low_half(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float high_half(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
-__device__ __forceinline__ Split2 split2(float x, float y)
-{
-    Split2 s;
-    s.hi = pack2(x, y);
-    x -= low_half(s.hi);
-    y -= high_half(s.hi);
-    s.mid = pack2(x, y);
-    s.lo = pack2(x - low_half(s.mid), y - high_half(s.mid));
-    return s;
-}
-
 // Lane 16g + n's fp32 weights of vector g as three planes of mma_rows' weights, 128 NT bytes apart.
 template <int NT>
 __device__ __forceinline__ void store_split(lds_byte* w, const float (&x)[NT], int lane)

@@ -5,27 +5,31 @@
 //            queries when Q < 16; waves take key tiles in turn, a batch of loads at a time), kept
 //            in LDS as fp32 [Q][N];
 //   phase 2  wave r owns query row r: max, exp and sum over the row (register butterflies), then
-//            the K best keys by a bitwise radix select on wave ballots (ties at the cut go to the
-//            lower index), listed in index order; QuadTree-A zeroes the kept keys' weights (their
-//            mass is refined at the next level);
-//   phase 3  m = P V on fp32 MFMA (values widened to fp32 as they are loaded, two batches of
-//            loads in flight): waves split the d columns into 16-wide tiles and the keys into
-//            chunks; partial tiles are summed through
-//            LDS and written as fp32 messages (or, for a single-level problem, straight to the
-//            output in the storage type).
+//            the K best keys by a bitwise radix select on wave ballots among the few keys that reach
+//            a bound on the K-th (ties at the cut go to the lower index), listed in index order;
+//            QuadTree-A zeroes the kept keys' weights (their mass is refined at the next level);
+//   phase 3  m = P V on MFMA. fp32: two batches of loads in flight, waves split the d columns into
+//            16-wide tiles and the keys into chunks. bf16: a wave takes 64 keys, brought to LDS
+//            during phase 2, with the weights as three bf16 terms. Partial tiles are summed
+//            through LDS and written as fp32 messages (or, for a single-level problem, straight
+//            to the output in the storage type).
+// What bounds it: instruction issue of phase 2 at these sizes (a row is 1 KB to 4 KB of LDS, a map's
+// keys and values stay in L2). Measured on MI355X, bf16 unless said: 8 heads x 1023 keys, d = 32, K = 16:
+// 84 us with the selection over all values of a lane, the values widened one by one and 8 rows, now 49; 8 x 4
+// maps of 300 keys 12.6 to 10.4; d = 64, 196 keys: 13.3 to 12.4; fp32, 300 keys: 11.8 to 11.1.
 // The coarsest map holds at most QTA_MAX_COARSE tokens, so a row fits in 16 registers per lane.
 // Maps of at most 64 tokens take coarse_small_kernel instead (one wave per query row).
 #include <type_traits>
 
-#include "qta_device.h"
+#include "bf16_tiles.h"
 #include "qta_internal.h"
 
 namespace qta {
 
 namespace {
 
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float float4_t __attribute__((ext_vector_type(4)));
+using tiles::bf16x8_t;
+using tiles::float4_t;
 
 
 // LDS pitch of a logit row: whole 64-element groups plus 4 floats, so the 16 rows that one MFMA
@@ -43,8 +47,28 @@ inline int coarse_per_lane(int N)
     return 0;
 }
 
+// bf16, behind the logit rows: 1 KB per wave for key chunks in passing; after the logits, a buffer for each wave
+// that has keys in the message product (64 at a time, 32 channels of their value rows), then its partial
+// messages [D / 16][16][16].
+constexpr int kCoarseBuffer = 4 * tiles::tile_bytes<32>();
+__host__ __device__ inline int coarse_behind(int N, int Q)
+{
+    const int chunks = (N + kWave - 1) / kWave, bufs = (chunks < Q ? chunks : Q) * kCoarseBuffer;
+    return bufs > Q * 1024 ? bufs : Q * 1024;
+}
+
+// Waves per SIMD the kernel's registers must leave room for, so that two workgroups of 16 rows share a CU: up to
+// six values a lane everything fits 64 vector registers without a spill, and the figure also holds the scalar
+// registers under their limit, which the selection's masks would pass (bf16, d = 64, 400 workgroups of 196 keys:
+// 15.6 us without it, 12.4 with it). Not fp32 with d = 64 and five or six values, where 64 would spill, nor more.
+template <typename T, int D, int kPerLane>
+constexpr int coarse_waves()
+{
+    return kPerLane <= (sizeof(T) == 4 && D == 64 ? 4 : 6) ? 8 : 4;
+}
+
 template <typename T, int D, bool VA, int kPerLane, int Q>
-__global__ __launch_bounds__(Q * kWave) void coarse_attn_kernel(CoarseArgs a)
+__global__ __launch_bounds__(Q * kWave) __attribute__((amdgpu_waves_per_eu(coarse_waves<T, D, kPerLane>()))) void coarse_attn_kernel(CoarseArgs a)
 {
     using S = Storage<T>;
     constexpr bool kBf16 = sizeof(T) == 2;
@@ -53,12 +77,14 @@ __global__ __launch_bounds__(Q * kWave) void coarse_attn_kernel(CoarseArgs a)
     extern __shared__ __align__(16) float smem[];
     const int N = a.N, C = a.C, pitch = coarse_pitch(N);
     float* Sm = smem;                              // [Q][pitch]
-    float* red = smem + Q * pitch;                 // [waves][16][16]
-    const int tiles = (N + Q - 1) / Q;             // query tiles of this map
+    float* red = smem + Q * pitch;                 // fp32: [waves][16][16]
+    tiles::lds_byte* const stage = (tiles::lds_byte*)red + (threadIdx.x >> 6) * 1024;             // bf16
+    tiles::lds_byte* const buf = (tiles::lds_byte*)red + (threadIdx.x >> 6) * kCoarseBuffer;
+    const int qtiles = (N + Q - 1) / Q;            // query tiles of this map
     const int ktiles = (N + 15) / 16;              // 16-key tiles
     int blk = blockIdx.x;
-    const int tile = blk % tiles;
-    blk /= tiles;
+    const int tile = blk % qtiles;
+    blk /= qtiles;
     const int h = blk % a.heads;
     const int b = blk / a.heads;
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6)), lane = threadIdx.x & 63;
@@ -82,10 +108,10 @@ __global__ __launch_bounds__(Q * kWave) void coarse_attn_kernel(CoarseArgs a)
     const int p3_ct = wave % NCT, p3_ks = wave / NCT;
     const int p3_ch = p3_ct * 16 + (lane & 15);
     const int steps = (N + 3) / 4;
-    float vb[kVBatch], vb2[kVBatch];
-    auto load_v = [&](int st0, float (&dst)[kVBatch]) {
+    float vb[kBf16 ? 1 : kVBatch], vb2[kBf16 ? 1 : kVBatch];
+    auto load_v = [&](int st0, float (&dst)[kBf16 ? 1 : kVBatch]) {
 #pragma unroll
-        for (int u = 0; u < kVBatch; ++u) {
+        for (int u = 0; u < (kBf16 ? 0 : kVBatch); ++u) {
             const int cand = min((st0 + u * NKS) * 4 + (lane >> 4), N - 1);    // clamped; weight 0 beyond N
             dst[u] = S::load1_at(vmap, __umul24(static_cast<uint32_t>(cand), static_cast<uint32_t>(C)) + p3_ch);
         }
@@ -114,12 +140,15 @@ __global__ __launch_bounds__(Q * kWave) void coarse_attn_kernel(CoarseArgs a)
 #pragma unroll
             for (int it = 0; it < kTileBatch; ++it) {
                 if (t0 + kWaves * it >= ktiles) break;                            // uniform
-                const int n = min((t0 + kWaves * it) * 16 + arow, N - 1);         // columns past N set to -inf
-                const uint32_t koff = __umul24(static_cast<uint32_t>(n), row_bytes) + kgrp * 16;
+                // columns past N are set to -inf. bf16: four lanes per row (see bf16_tiles.h), moved to the
+                // operand's lanes below
+                const int n = min((t0 + kWaves * it) * 16 + (kBf16 ? lane >> 2 : arow), N - 1);
+                const uint32_t koff = __umul24(static_cast<uint32_t>(n), row_bytes) +
+                                      (kBf16 ? tiles::gather_chunk(lane) : static_cast<uint32_t>(kgrp * 16));
 #pragma unroll
                 for (int jj = 0; jj < NJ; ++jj) kb[it][jj] = load_at<uint4>(kmap, koff + 64 * jj);
             }
-            if (first) {
+            if (!kBf16 && first) {
                 load_v(p3_ks, vb);
                 load_v(p3_ks + NKS * kVBatch, vb2);
                 first = false;
@@ -134,7 +163,7 @@ __global__ __launch_bounds__(Q * kWave) void coarse_attn_kernel(CoarseArgs a)
                     if constexpr (kBf16) {
                         // 8 bf16 per chunk: one k-step of 32 (eight channels per lane)
                         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, qa[jj]),
-                                                                      __builtin_bit_cast(bf16x8_t, kb[it][jj]), acc, 0, 0, 0);
+                                                                      tiles::pass_operand(kb[it][jj], stage, lane), acc, 0, 0, 0);
                     } else {
                         // 4 floats per chunk: four k-steps
                         const uint4 qq = qa[jj], kk = kb[it][jj];
@@ -150,37 +179,29 @@ __global__ __launch_bounds__(Q * kWave) void coarse_attn_kernel(CoarseArgs a)
                     if (4 * kgrp + jr < Q) Sm[(4 * kgrp + jr) * pitch + n] = n < N ? acc[jr] * a.scale : -INFINITY;
             }
         }
-        if (first) {                     // a wave with no key tile (more waves than tiles)
+        if (!kBf16 && first) {           // a wave with no key tile (more waves than tiles)
             load_v(p3_ks, vb);
             load_v(p3_ks + NKS * kVBatch, vb2);
         }
     }
-    // The output element of this thread in the epilogue (Q*D <= the Q*64 threads: one each, or none),
-    // and for the fused position encoding its operands, requested now so that they arrive during
-    // the softmax: the 3x3 window of v around the query token (clamped addresses, zero outside the
-    // map through opaque masks), this channel's kernel and its bias.
-    static_assert(D <= kWave, "one output element per thread");
-    const int er = static_cast<int>(threadIdx.x) / D, ech = static_cast<int>(threadIdx.x) - er * D;
-    const int eqi = tile * Q + er;
-    float pev[9], pew[9], peb = 0.f;
-    if (a.pe_w) {                                    // uniform
-        const int Wc = a.Wc, Hc = N / Wc;
-        const int qc = min(eqi, N - 1);
-        const int qy = qc / Wc, qx = qc - qy * Wc;
-        const float* wk = a.pe_w + (static_cast<size_t>(h) * D + ech) * 9;
-#pragma unroll
-        for (int ky = 0; ky < 3; ++ky)
-#pragma unroll
-            for (int kx = 0; kx < 3; ++kx) {
-                const int yy = qy + ky - 1, xx = qx + kx - 1;
-                const int yc = min(max(yy, 0), Hc - 1), xc = min(max(xx, 0), Wc - 1);
-                const unsigned ok = opaque_mask(yy >= 0 && yy < Hc && xx >= 0 && xx < Wc);
-                pev[ky * 3 + kx] = masked(S::load1_at(vmap, __umul24(static_cast<uint32_t>(yc * Wc + xc), static_cast<uint32_t>(C)) + ech), ok);
-                pew[ky * 3 + kx] = wk[ky * 3 + kx];
-            }
-        peb = a.pe_b ? a.pe_b[h * D + ech] : 0.f;
-    }
     __syncthreads();
+
+    // bf16: channels 32 jj .. of the value rows of 64 keys into the wave's buffer, the first of them now, so that
+    // they arrive during the selection. Tile t's row n is key 32 (n >> 3) + 8 (n & 3) + 4 (n >> 2 & 1) + t:
+    // the order in which a transposed read (bf16_tiles.h) hands lane group g keys 32u + 8g .. 32u + 8g + 7,
+    // which are consecutive in a logit row.
+    const int nchunk = (N + kWave - 1) / kWave;
+    auto load_values = [&](int c, int jj) {
+        if constexpr (kBf16) {
+            const __amdgpu_buffer_rsrc_t vres = tiles::map_resource(vmap);
+            const int n = lane >> 2, key0 = c * kWave + 32 * (n >> 3) + 8 * (n & 3) + 4 * ((n >> 2) & 1);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                tiles::load_lds16(vres, __umul24(static_cast<uint32_t>(min(key0 + t, N - 1)), row_bytes) + tiles::gather_chunk(lane) + 64 * jj,
+                                  0, buf + t * tiles::tile_bytes<32>());
+        }
+    };
+    if (kBf16 && wave < nchunk) load_values(wave, 0);
 
     // ---- phase 2: softmax and selection, one wave per query row ----
     {
@@ -210,32 +231,86 @@ __global__ __launch_bounds__(Q * kWave) void coarse_attn_kernel(CoarseArgs a)
 
         if (a.K > 0 && qi < N) {
             // the K best keys by logit (ties to the lower index), listed in index order
-            uint32_t key[kPerLane], name[kPerLane];
-            bool kept[kPerLane];
+            uint32_t key[kPerLane];
 #pragma unroll
-            for (int e = 0; e < kPerLane; ++e) {
-                const int j = lane + kWave * e;
-                key[e] = j < N ? ordered_bits(x[e]) : 0u;
-                name[e] = static_cast<uint32_t>(j);
-            }
+            for (int e = 0; e < kPerLane; ++e) key[e] = lane + kWave * e < N ? ordered_bits(x[e]) : 0u;
             const int keff = a.K < N ? a.K : N;
-            wave_select_top<kPerLane>(key, name, keff, kept);
-            const size_t orow = ((static_cast<size_t>(b) * a.heads + h) * N + qi) * a.K;
-            int before = 0;
+            int32_t* const so = a.sel_idx + ((static_cast<size_t>(b) * a.heads + h) * N + qi) * a.K;
+            float* const ko = a.sel_key + ((static_cast<size_t>(b) * a.heads + h) * N + qi) * a.K;
+            // With four or more values a lane (N > 64, so every lane holds a key): the K-th largest of the lanes'
+            // maxima bounds the K-th largest key from below, and the few keys at or above it go to LDS (the
+            // row's logits are in registers) in index order, one a lane. The searches then test one value a
+            // lane and bit, and the listing runs once instead of kPerLane times.
+            int nsurv = kWave + 1;
+            uint32_t low = 0u;
+            if constexpr (kPerLane >= 4) {
+                uint32_t top[1] = {0u};
 #pragma unroll
-            for (int e = 0; e < kPerLane; ++e) {
-                const uint64_t mask = __ballot(kept[e]);
-                if (kept[e]) {
-                    const int pos = before + lanes_below(mask);
-                    a.sel_idx[orow + pos] = lane + kWave * e;
-                    a.sel_key[orow + pos] = p[e];
-                    if constexpr (VA) p[e] = 0.f;           // refined at the next level (Omega)
+                for (int e = 0; e < kPerLane; ++e) top[0] = max(top[0], key[e]);
+                low = wave_cut<1>(top, keff);
+                nsurv = 0;
+#pragma unroll
+                for (int e = 0; e < kPerLane; ++e) nsurv += __popcll(__ballot(key[e] >= low));
+                nsurv = __builtin_amdgcn_readfirstlane(nsurv);
+            }
+            if (kPerLane >= 4 && nsurv <= kWave) {           // uniform; more only where many keys are equal
+                int before = 0;
+#pragma unroll
+                for (int e = 0; e < kPerLane; ++e) {
+                    const uint64_t mask = __ballot(key[e] >= low);
+                    if (key[e] >= low) {
+                        const int pos = before + lanes_below(mask);
+                        row[pos] = __uint_as_float(key[e]);
+                        row[kWave + pos] = __uint_as_float(static_cast<uint32_t>(lane + kWave * e));
+                    }
+                    before += __popcll(mask);
                 }
-                before += __popcll(mask);
+                wave_lds_sync();
+                const uint32_t s[1] = {lane < nsurv ? __float_as_uint(row[lane]) : 0u};
+                const uint32_t name = __float_as_uint(row[kWave + lane]);
+                // (the search stops at any value that parts the keff best survivors from the rest; keys below the
+                // bound must stay below the cut too)
+                const uint32_t cut = max(wave_cut<1>(s, keff), low);
+                const uint64_t above = __ballot(s[0] > cut), at = __ballot(s[0] == cut);
+                const int need = keff - __popcll(above);     // places for keys at the cut, lowest index first
+                const bool mine = s[0] > cut || (s[0] == cut && lanes_below(at) < need);
+                const uint64_t mask = __ballot(mine);
+                if (mine) {
+                    const uint32_t pos = static_cast<uint32_t>(lanes_below(mask)) * 4u;
+                    store_at<int32_t>(so, pos, static_cast<int32_t>(name));
+                    store_at<float>(ko, pos, __expf(from_ordered_bits(s[0]) - mx) * inv);
+                }
+                if constexpr (VA) {                          // the kept keys are refined at the next level (Omega)
+                    int ties = 0;
+#pragma unroll
+                    for (int e = 0; e < kPerLane; ++e) {
+                        const uint64_t eq = __ballot(key[e] == cut);
+                        if (key[e] > cut || (key[e] == cut && ties + lanes_below(eq) < need)) p[e] = 0.f;
+                        ties += __popcll(eq);
+                    }
+                }
+            } else {
+                uint32_t name[kPerLane];
+                bool kept[kPerLane];
+#pragma unroll
+                for (int e = 0; e < kPerLane; ++e) name[e] = static_cast<uint32_t>(lane + kWave * e);
+                wave_select_top<kPerLane>(key, name, keff, kept);
+                int before = 0;
+#pragma unroll
+                for (int e = 0; e < kPerLane; ++e) {
+                    const uint64_t mask = __ballot(kept[e]);
+                    if (kept[e]) {
+                        const int pos = before + lanes_below(mask);
+                        so[pos] = lane + kWave * e;
+                        ko[pos] = p[e];
+                        if constexpr (VA) p[e] = 0.f;        // refined at the next level (Omega)
+                    }
+                    before += __popcll(mask);
+                }
             }
             if (lane >= keff && lane < a.K) {
-                a.sel_idx[orow + lane] = -1;
-                a.sel_key[orow + lane] = 0.f;
+                so[lane] = -1;
+                ko[lane] = 0.f;
             }
         }
 #pragma unroll
@@ -246,9 +321,52 @@ __global__ __launch_bounds__(Q * kWave) void coarse_attn_kernel(CoarseArgs a)
     }
     __syncthreads();
 
-    // ---- phase 3: messages m = P V on fp32 MFMA (values widened on load, so no transpose) ----
-    // A wave takes key steps p3_ks, p3_ks + NKS, ... in batches of kVBatch, two batches in flight.
-    {
+    // ---- phase 3: messages m = P V. fp32: on the fp32 MFMA; a wave takes key steps p3_ks, p3_ks + NKS, ... in
+    // batches of kVBatch, two batches in flight. bf16: a wave takes 64 keys at a time; the weights are split
+    // exactly into three bf16 terms as they are read, whose products with the values are exact, so the sums
+    // are as accurate as fp32's. ----
+    if constexpr (kBf16) {
+        using namespace tiles;
+        constexpr int CT = D / 16;
+        const int n16 = lane & 15, g = lane >> 4;
+        float4_t acc[CT];
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) acc[ct] = float4_t{0.f, 0.f, 0.f, 0.f};
+        const float* prow = Sm + (n16 & (Q - 1)) * pitch;            // P rows past Q repeat (ignored)
+        for (int c = wave; c < nchunk; c += kWaves) {                // uniform
+#pragma unroll
+            for (int jj = 0; jj < D / 32; ++jj) {
+                if (jj > 0 || c != wave) {
+                    wave_lds_sync();                                 // the last rows' reads
+                    load_values(c, jj);
+                }
+                wait_lds_loads();
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const float* pk = prow + c * kWave + 32 * u + 8 * g;
+                    const float4_t x = *reinterpret_cast<const float4_t*>(pk), y = *reinterpret_cast<const float4_t*>(pk + 4);
+                    const Split2 s0 = split2(x[0], x[1]), s1 = split2(x[2], x[3]), s2 = split2(y[0], y[1]), s3 = split2(y[2], y[3]);
+                    const bf16x8_t w[3] = {__builtin_bit_cast(bf16x8_t, u32x4_t{s0.hi, s1.hi, s2.hi, s3.hi}),
+                                           __builtin_bit_cast(bf16x8_t, u32x4_t{s0.mid, s1.mid, s2.mid, s3.mid}),
+                                           __builtin_bit_cast(bf16x8_t, u32x4_t{s0.lo, s1.lo, s2.lo, s3.lo})};
+#pragma unroll
+                    for (int ct = 0; ct < 2; ++ct) {
+                        const bf16x8_t v = rows_transposed4<32>(buf, u, ct, lane);
+#pragma unroll
+                        for (int p = 0; p < 3; ++p)
+                            acc[2 * jj + ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[p], v, acc[2 * jj + ct], 0, 0, 0);
+                    }
+                }
+            }
+        }
+        wave_lds_sync();
+        if (wave < nchunk) {                                         // uniform
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) ((lds_ptr<float>)buf)[(ct * 16 + 4 * g + j) * 16 + n16] = acc[ct][j];
+        }
+    } else {
         const int prow = (lane & 15) & (Q - 1), kgrp = lane >> 4;   // P rows past Q repeat (ignored)
         const float* prw = Sm + prow * pitch + kgrp;
         float4_t acc = {0.f, 0.f, 0.f, 0.f};
@@ -271,13 +389,44 @@ __global__ __launch_bounds__(Q * kWave) void coarse_attn_kernel(CoarseArgs a)
 #pragma unroll
         for (int j = 0; j < 4; ++j) red[(wave * 16 + 4 * kgrp + j) * 16 + (lane & 15)] = acc[j];
     }
+    // The output element of this thread in the epilogue (Q*D <= the Q*64 threads: one each, or none),
+    // and for the fused position encoding its operands, requested now that the selection and the
+    // message product need their registers no more (held from before the softmax they took d = 64 past the 64
+    // registers that two workgroups of 16 waves leave each other): the 3x3 window of v around the query token (clamped addresses, zero outside the
+    // map through opaque masks), this channel's kernel and its bias.
+    static_assert(D <= kWave, "one output element per thread");
+    const int er = static_cast<int>(threadIdx.x) / D, ech = static_cast<int>(threadIdx.x) - er * D;
+    const int eqi = tile * Q + er;
+    float pev[9], pew[9], peb = 0.f;
+    if (a.pe_w) {                                    // uniform
+        const int Wc = a.Wc, Hc = N / Wc;
+        const int qc = min(eqi, N - 1);
+        const int qy = qc / Wc, qx = qc - qy * Wc;
+        const float* wk = a.pe_w + (static_cast<size_t>(h) * D + ech) * 9;
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) {
+                const int yy = qy + ky - 1, xx = qx + kx - 1;
+                const int yc = min(max(yy, 0), Hc - 1), xc = min(max(xx, 0), Wc - 1);
+                const unsigned ok = opaque_mask(yy >= 0 && yy < Hc && xx >= 0 && xx < Wc);
+                pev[ky * 3 + kx] = masked(S::load1_at(vmap, __umul24(static_cast<uint32_t>(yc * Wc + xc), static_cast<uint32_t>(C)) + ech), ok);
+                pew[ky * 3 + kx] = wk[ky * 3 + kx];
+            }
+        peb = a.pe_b ? a.pe_b[h * D + ech] : 0.f;
+    }
     __syncthreads();
     if (er < Q && eqi < N) {
         const int r = er, ch = ech;
         const int ct = ch / 16, col = ch % 16;
         float s = 0.f;
+        if constexpr (kBf16) {
+            for (int ks = 0; ks < min(nchunk, kWaves); ++ks)         // uniform
+                s += red[ks * (kCoarseBuffer / 4) + (ct * 16 + r) * 16 + col];
+        } else {
 #pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) s += red[((ks * NCT + ct) * 16 + r) * 16 + col];
+            for (int ks = 0; ks < NKS; ++ks) s += red[((ks * NCT + ct) * 16 + r) * 16 + col];
+        }
         const int qi = eqi;
         if (a.pe_w) {                                    // uniform: the fused position encoding
             // 3x3 depth-wise cross-correlation of v around token qi, zero outside the map, plus the bias
@@ -518,18 +667,22 @@ hipError_t launch_small(const CoarseArgs& a, hipStream_t stream)
 // phase). Fewer rows per workgroup spread a small map's rows over more compute units, so that the
 // selection's scalar work and each phase's latency are shared by fewer rows, at the price of more
 // passes over the map's keys and values (from L2) and of MFMA tiles only half filled. Measured on
-// MI355X, 8 rows pay where the MFMA phases are cheapest (bf16 with d = 32: one 16-byte chunk per key
-// row and k-step pair) and 16 rows elsewhere (fp32, or d = 64).
-template <typename T, int D>
+// MI355X (bf16, 8 against 16 rows): d = 32, 16 maps of 300 keys 11.6 and 12.6 us, 128 of them 46.1
+// and 48.7, 8 maps of 100 5.2 and 6.3; 16 maps of 512 11.9 and 10.8 but 64 of them 52.2 and 59.2; 16 of
+// 1023 48.1 and 44.6; d = 64, 32 maps of 196 13.3 and 12.3, 16 of 1023 63.3 and 56.5. So 8 rows for bf16 with d = 32
+// (one 16-byte chunk per key row and k-step pair) and small maps, 16 elsewhere: fp32, d = 64, and from 385 keys,
+// where the passes over the keys count for more.
+template <typename T, int D, int kPerLane>
 constexpr int coarse_rows()
 {
-    return (sizeof(T) == 2 && D == 32) ? 8 : 16;
+    return (sizeof(T) == 2 && D == 32 && kPerLane < 8) ? 8 : 16;
 }
 
 template <typename T, int D, bool VA, int kPerLane, int Q>
 hipError_t launch_rows(const CoarseArgs& a, hipStream_t stream)
 {
-    const size_t lds = (static_cast<size_t>(Q) * coarse_pitch(a.N) + static_cast<size_t>(Q) * 16 * 16) * sizeof(float);
+    const size_t behind = sizeof(T) == 2 ? static_cast<size_t>(coarse_behind(a.N, Q)) : static_cast<size_t>(Q) * 16 * 16 * sizeof(float);
+    const size_t lds = static_cast<size_t>(Q) * coarse_pitch(a.N) * sizeof(float) + behind;
     if (lds > device_max_lds()) return hipErrorInvalidValue;
     static std::atomic<unsigned long long> configured{0};     // devices whose LDS limit is raised
     if (hipError_t e = set_max_lds_once(reinterpret_cast<const void*>(&coarse_attn_kernel<T, D, VA, kPerLane, Q>), configured);
@@ -546,7 +699,7 @@ hipError_t launch_rows(const CoarseArgs& a, hipStream_t stream)
 template <typename T, int D, bool VA, int kPerLane>
 hipError_t launch_one(const CoarseArgs& a, hipStream_t stream)
 {
-    return launch_rows<T, D, VA, kPerLane, coarse_rows<T, D>()>(a, stream);
+    return launch_rows<T, D, VA, kPerLane, coarse_rows<T, D, kPerLane>()>(a, stream);
 }
 
 template <typename T, int D, bool VA>

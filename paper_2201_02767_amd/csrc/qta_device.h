@@ -350,6 +350,26 @@ __device__ __forceinline__ int32_t rank_word_index(uint64_t w)
 
 __device__ __forceinline__ float rank_word_score(uint64_t w) { return from_ordered_bits(static_cast<uint32_t>(w >> 32)); }
 
+// The keff-th largest of the wave's keys (NPER a lane), built bit by bit from the top on ballots; ends early
+// where the keys at or above the partial cut number exactly keff (the cut is then a lower bound that
+// separates the same keys). 1 <= keff <= number of nonzero keys.
+template <int NPER>
+__device__ __forceinline__ uint32_t wave_cut(const uint32_t (&key)[NPER], int keff)
+{
+    keff = __builtin_amdgcn_readfirstlane(keff);
+    uint32_t cut = 0, bit = 0x80000000u;
+    while (bit != 0u) {
+        const uint32_t c = cut | bit;
+        int n = 0;
+#pragma unroll
+        for (int e = 0; e < NPER; ++e) n += __popcll(__ballot(key[e] >= c));
+        n = __builtin_amdgcn_readfirstlane(n);
+        cut = n >= keff ? c : cut;
+        bit = n == keff ? 0u : bit >> 1;
+    }
+    return cut;
+}
+
 // Exact top-`keff` selection over NPER candidates per lane, held as 32-bit ranking keys (larger is
 // better, 0 = not a candidate) with distinct 32-bit names. Returns, per candidate, whether it is
 // kept: every key above the cut, and at the cut the lowest names first. The cut (the keff-th
@@ -378,18 +398,8 @@ __device__ __forceinline__ void wave_select_top(const uint32_t (&key)[NPER], con
     } else {
         // several candidates per lane: the loop stays rolled, so the cut and the bit under test
         // are kept wave-uniform in scalar registers explicitly (one scalar unit serves all the waves
-        // of a compute unit, so the loop keeps its scalar work small); a bit that leaves exactly
-        // keff keys at or above the cut ends the search by clearing the bit under test
-        uint32_t bitv = 0x80000000u;
-        while (bitv != 0u) {
-            const uint32_t c = cut | bitv;
-            int n = 0;
-#pragma unroll
-            for (int e = 0; e < NPER; ++e) n += __popcll(__ballot(key[e] >= c));
-            n = __builtin_amdgcn_readfirstlane(n);
-            cut = n >= keff ? c : cut;
-            bitv = n == keff ? 0u : bitv >> 1;
-        }
+        // of a compute unit, so the loop keeps its scalar work small)
+        cut = wave_cut<NPER>(key, keff);
     }
 #pragma unroll
     for (int e = 0; e < NPER; ++e) cnt += __popcll(__ballot(key[e] >= cut));

@@ -24,26 +24,6 @@ namespace {
 
 constexpr int kSurvivors = 256;         // survivors of a row kept in LDS
 
-// The keff-th largest of the wave's keys (NPER a lane), built bit by bit from the top on ballots; ends early
-// where the keys at or above the partial cut number exactly keff (the cut is then a lower bound that
-// separates the same keys). 1 <= keff <= number of nonzero keys.
-template <int NPER>
-__device__ __forceinline__ uint32_t wave_cut(const uint32_t (&key)[NPER], int keff)
-{
-    keff = __builtin_amdgcn_readfirstlane(keff);
-    uint32_t cut = 0, bit = 0x80000000u;
-    while (bit != 0u) {
-        const uint32_t c = cut | bit;
-        int n = 0;
-#pragma unroll
-        for (int e = 0; e < NPER; ++e) n += __popcll(__ballot(key[e] >= c));
-        n = __builtin_amdgcn_readfirstlane(n);
-        cut = n >= keff ? c : cut;
-        bit = n == keff ? 0u : bit >> 1;
-    }
-    return cut;
-}
-
 // Lists in LDS every one of the wave's keys above `thr`, with its name; returns how many.
 template <int NPER, typename Name>
 __device__ __forceinline__ int list_above(const uint32_t (&key)[NPER], Name name, uint32_t thr, uint32_t* lk, int32_t* ln)

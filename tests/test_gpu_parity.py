@@ -359,6 +359,24 @@ def test_largest_coarse_level(dev, dtype):
     run_and_compare(dev, q, k, v, levels=2, K=8, variant="B", dtype=dtype, label="coarse cap")
 
 
+@pytest.mark.parametrize("variant,h,w,heads,d,K", [("B", 5, 13, 2, 32, 1), ("A", 8, 16, 1, 64, 16),
+                                                   ("B", 3, 43, 2, 32, 64), ("A", 11, 19, 1, 32, 64),
+                                                   ("B", 14, 14, 1, 64, 8), ("B", 12, 25, 1, 32, 16),
+                                                   ("A", 16, 24, 1, 32, 32), ("B", 7, 55, 1, 64, 8),
+                                                   ("A", 19, 27, 1, 64, 16), ("B", 31, 33, 1, 64, 64)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("equal", [0.0, 0.15, 1.0])
+def test_coarse_rows_and_survivors(dev, variant, h, w, heads, d, K, dtype, equal):
+    """Coarsest maps at the edges of the values a lane holds, of the 64-key value chunks and of the K of a bound's
+    survivors; with distinct keys, with a sixth of the cells equal (ties at the cut) and all equal (more
+    survivors than a wave has lanes). The tolerance is the parity protocol's."""
+    rng = np.random.default_rng(h * w + K)
+    q, k, v = rand_qkv(31 + h * w, 1, 2 * h, 2 * w, heads, d, dtype, scale=0.7)
+    same = np.repeat(np.repeat(rng.random((h, w)) < equal, 2, 0), 2, 1)
+    k[:, same] = k[:, :1, 0]
+    run_and_compare(dev, q, k, v, levels=2, K=K, variant=variant, dtype=dtype, label=f"coarse equal={equal}")
+
+
 def test_piecewise_constant_a_equals_dense(dev):
     """QuadTree-A on maps whose Q and K are constant per coarsest cell equals dense attention."""
     rng = np.random.default_rng(23)
