@@ -21,6 +21,7 @@
 //      MFMA and without atomics
 //   4. pyramids: a pooled token hands 1/n of its gradient to each of its n valid children; the
 //      level-0 gradients add every ancestor's, scaled along the chain      (bwd_unpool_kernel)
+// The passes of 2 are written here for fp32; bf16 maps take those of bwd_bf16.h, and the launchers below pick.
 // All gradients are fp32. The message gradients of levels >= 2 are summed with atomics and the
 // parents within one kept key's list come in the order the query pass's count atomics hand out, so
 // the last bits of the gradients may differ between runs.
@@ -32,7 +33,6 @@ namespace qta {
 namespace {
 
 typedef float float4_t __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 // ---------------------------------------------------------------------------------------------
 // zero fill (no hipMemsetAsync: the launch sequence may be captured in a graph)
@@ -62,7 +62,7 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(FillArgs a)
 // operand of dq) and per slot the four queries' logit gradients.
 struct BwdLds {
     int ks, dx, total;
-    int kpitch;     // elements per key row (bf16 rows stay bf16: exact, and half the LDS per wave)
+    int kpitch;     // elements per key row
 };
 
 template <typename T, int D>
@@ -70,12 +70,7 @@ __host__ __device__ inline BwdLds bwd_lds(int nsp)
 {
     constexpr int TB = sizeof(T);
     BwdLds L;
-    // rows of 16-byte multiples; bf16 rows with d = 32 unpadded: the dq loop's two slot halves are 32
-    // rows apart and meet the same banks with a padded pitch as well, the row writes conflict more,
-    // and the 5 KB a wave then takes with 64 slots lets LDS hold 8 waves per SIMD instead of 6, which
-    // outweighs that (d = 64 keeps its padding: unpadded it measured slower, with registers, not
-    // LDS, bounding its occupancy)
-    L.kpitch = TB == 2 ? (D == 32 ? D : D + 8) : D + 4;
+    L.kpitch = D + 4;                                      // rows of 16-byte multiples
     L.ks = 0;
     L.dx = L.ks + nsp * L.kpitch * TB;
     L.total = L.dx + nsp * 16;
@@ -100,7 +95,6 @@ template <typename T, int D, int NSP, bool VA, bool FINEST>
 __device__ __forceinline__ void bwd_item(const BwdLevelArgs& a, const int item, unsigned char* const base)
 {
     using S = Storage<T>;
-    constexpr bool kBf16 = sizeof(T) == 2;
     constexpr int TB = sizeof(T);
     constexpr int RB = D * TB;             // bytes of one head's row
     constexpr int E = S::kPer16B;          // elements per 16-byte chunk
@@ -244,21 +238,13 @@ __device__ __forceinline__ void bwd_item(const BwdLevelArgs& a, const int item, 
         for (int j = 0; j < NJ; ++j) {
             const uint4 kk = gok[t] ? kc[j] : make_uint4(0, 0, 0, 0);
             const uint4 vv = gok[t] ? vc[j] : make_uint4(0, 0, 0, 0);
-            if constexpr (kBf16) {
-                ax = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, qa[j]),
-                                                             __builtin_bit_cast(bf16x8_t, kk), ax, 0, 0, 0);
-            } else {
-                ax = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(qa[j].x), __uint_as_float(kk.x), ax, 0, 0, 0);
-                ax = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(qa[j].y), __uint_as_float(kk.y), ax, 0, 0, 0);
-                ax = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(qa[j].z), __uint_as_float(kk.z), ax, 0, 0, 0);
-                ax = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(qa[j].w), __uint_as_float(kk.w), ax, 0, 0, 0);
-            }
+            ax = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(qa[j].x), __uint_as_float(kk.x), ax, 0, 0, 0);
+            ax = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(qa[j].y), __uint_as_float(kk.y), ax, 0, 0, 0);
+            ax = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(qa[j].z), __uint_as_float(kk.z), ax, 0, 0, 0);
+            ax = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(qa[j].w), __uint_as_float(kk.w), ax, 0, 0, 0);
             float vf[E];
             S::unpack(vv, vf);
-            if constexpr (FINEST && kBf16) {
-                ag = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, da[j]),
-                                                             __builtin_bit_cast(bf16x8_t, vv), ag, 0, 0, 0);
-            } else if constexpr (FINEST) {
+            if constexpr (FINEST) {
                 ag = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(da[j].x), vf[0], ag, 0, 0, 0);
                 ag = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(da[j].y), vf[1], ag, 0, 0, 0);
                 ag = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(da[j].z), vf[2], ag, 0, 0, 0);
@@ -269,11 +255,7 @@ __device__ __forceinline__ void bwd_item(const BwdLevelArgs& a, const int item, 
                     ag = __builtin_amdgcn_mfma_f32_16x16x4f32(dmA[j][e], vf[e], ag, 0, 0, 0);
             }
             // the key row in the storage type (zeros for missing candidates)
-            if constexpr (kBf16) {
-                *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(Ks) + s * lay.kpitch + (g + 4 * j) * E) = kk;
-            } else {
-                *reinterpret_cast<uint4*>(Ks + s * lay.kpitch + (g + 4 * j) * E) = kk;
-            }
+            *reinterpret_cast<uint4*>(Ks + s * lay.kpitch + (g + 4 * j) * E) = kk;
         }
         // rows 4g .. 4g+3 of the products are all query g
         acc_x[t] = ax[0];
@@ -392,12 +374,7 @@ __device__ __forceinline__ void bwd_item(const BwdLevelArgs& a, const int item, 
         float4_t o = {0.f, 0.f, 0.f, 0.f};
         for (int st = 0; st < sph; ++st) {
             const int sl = hh * sph + st;
-            float kv;
-            if constexpr (kBf16)
-                kv = bf16_bits_to_f32(reinterpret_cast<const uint16_t*>(Ks)[sl * lay.kpitch + 4 * cg + t4]);
-            else
-                kv = Ks[sl * lay.kpitch + 4 * cg + t4];
-            o = __builtin_amdgcn_mfma_f32_4x4x1f32(dxs[sl * 4 + t4], kv, o, 0, 0, 0);
+            o = __builtin_amdgcn_mfma_f32_4x4x1f32(dxs[sl * 4 + t4], Ks[sl * lay.kpitch + 4 * cg + t4], o, 0, 0, 0);
         }
         if constexpr (NH == 2) {
 #pragma unroll
@@ -788,27 +765,16 @@ __global__ __launch_bounds__(256) void bwd_fill_kernel(BwdFillArgs a)
 // the L2.)
 struct KeyLds {
     int rows, dx, vw, total;
-    int qpitch;     // elements per query row
-    int mpitch;     // elements per dm row
-    int mslots;     // dm rows the buffer holds at once (all 64, or 32 per pass)
+    int pitch;      // elements per row
 };
 
-// With bf16 inputs the query rows are bf16 values and stay bf16 (exact, half the LDS). So do the
-// finest level's dm rows, which are dout (its w_0 moves into the weights vw). The coarser levels'
-// dm rows are fp32 and go through the buffer 32 slots at a time, so that it stays at the size of
-// the bf16 query rows.
-template <typename T, int D, bool FINEST>
+template <int D>
 __host__ __device__ inline KeyLds key_lds()
 {
-    constexpr bool bf = sizeof(T) == 2;
     KeyLds L;
-    L.qpitch = bf ? D + 8 : D + 4;                         // rows of 16-byte multiples
-    L.mpitch = bf && FINEST ? D + 8 : D + 4;
-    L.mslots = bf && !FINEST ? 2 * kKeyChunk : 4 * kKeyChunk;
-    const int qbytes = 4 * kKeyChunk * L.qpitch * (bf ? 2 : 4);
-    const int mbytes = L.mslots * L.mpitch * (bf && FINEST ? 2 : 4);
+    L.pitch = D + 4;                                       // rows of 16-byte multiples
     L.rows = 0;
-    L.dx = L.rows + (qbytes > mbytes ? qbytes : mbytes);
+    L.dx = L.rows + 4 * kKeyChunk * L.pitch * 4;
     L.vw = L.dx;                                           // the weights replace dx once dk is done
     L.total = L.dx + 4 * kKeyChunk * 16;
     return L;
@@ -818,7 +784,6 @@ template <typename T, int D, bool VA, bool FINEST>
 __global__ __launch_bounds__(64) void bwd_key_kernel(BwdLevelArgs a)
 {
     using S = Storage<T>;
-    constexpr bool kBf16 = sizeof(T) == 2;
     constexpr int TB = sizeof(T);
     constexpr int RB = D * TB;               // bytes of one head's row (storage)
     constexpr int E = S::kPer16B;            // storage elements per 16-byte chunk
@@ -839,18 +804,7 @@ __global__ __launch_bounds__(64) void bwd_key_kernel(BwdLevelArgs a)
     if (static_cast<int>(blockIdx.x) >= nchunks) return;    // whole wave
     const int chunk = __builtin_amdgcn_readfirstlane(xcd_remap(static_cast<int>(blockIdx.x), nchunks));
     extern __shared__ __align__(16) unsigned char smem[];
-    const KeyLds lay = key_lds<T, D, FINEST>();
-    constexpr bool kRows16 = kBf16 && FINEST;                // query and dm rows kept as bf16
-    constexpr bool kSplit = kBf16 && !FINEST;                // bf16 query rows, fp32 dm rows in two passes
-    uint16_t* const Rs16 = reinterpret_cast<uint16_t*>(smem + lay.rows);
-    auto q_elem = [&](int sl, int c) -> float {
-        if constexpr (kBf16) return bf16_bits_to_f32(Rs16[sl * lay.qpitch + c]);
-        else return reinterpret_cast<const float*>(smem + lay.rows)[sl * lay.qpitch + c];
-    };
-    auto m_elem = [&](int sl, int c) -> float {
-        if constexpr (kRows16) return bf16_bits_to_f32(Rs16[sl * lay.mpitch + c]);
-        else return reinterpret_cast<const float*>(smem + lay.rows)[sl * lay.mpitch + c];
-    };
+    const KeyLds lay = key_lds<D>();
     float* Rs = reinterpret_cast<float*>(smem + lay.rows);    // q rows, then dm rows
     float* dxs = reinterpret_cast<float*>(smem + lay.dx);     // [slot][4 keys]
     float* vws = reinterpret_cast<float*>(smem + lay.vw);
@@ -894,19 +848,11 @@ __global__ __launch_bounds__(64) void bwd_key_kernel(BwdLevelArgs a)
 #pragma unroll
         for (int j = 0; j < NJF; ++j) {
             const int c0 = (g + 4 * j) * 4;
-            if constexpr (kBf16) {
-                const uint2 vr = *reinterpret_cast<const uint2*>(static_cast<const unsigned char*>(a.v) + krow + c0 * 2);
-                vAf[j][0] = bf16_bits_to_f32(vr.x & 0xFFFFu);
-                vAf[j][1] = bf16_bits_to_f32(vr.x >> 16);
-                vAf[j][2] = bf16_bits_to_f32(vr.y & 0xFFFFu);
-                vAf[j][3] = bf16_bits_to_f32(vr.y >> 16);
-            } else {
-                const float4 vr = *reinterpret_cast<const float4*>(static_cast<const unsigned char*>(a.v) + krow + c0 * 4);
-                vAf[j][0] = vr.x;
-                vAf[j][1] = vr.y;
-                vAf[j][2] = vr.z;
-                vAf[j][3] = vr.w;
-            }
+            const float4 vr = *reinterpret_cast<const float4*>(static_cast<const unsigned char*>(a.v) + krow + c0 * 4);
+            vAf[j][0] = vr.x;
+            vAf[j][1] = vr.y;
+            vAf[j][2] = vr.z;
+            vAf[j][3] = vr.w;
 #pragma unroll
             for (int e = 0; e < 4; ++e) vAf[j][e] = masked(vAf[j][e], km);
         }
@@ -937,9 +883,8 @@ __global__ __launch_bounds__(64) void bwd_key_kernel(BwdLevelArgs a)
     const float* const m_base = FINEST ? nullptr : a.dm + static_cast<size_t>(b) * N * C + h * D;
     const float* const w_base = a.w ? a.w + static_cast<size_t>(b) * N * a.heads * a.levels : nullptr;
     float acc_x[4] = {0.f, 0.f, 0.f, 0.f}, acc_g[4] = {0.f, 0.f, 0.f, 0.f};
-    // each tile's dm chunks (level 0: w_0 dout; bf16: dout as stored), kept for dv
-    float mreg[NT][kRows16 ? 1 : (FINEST ? NJ * E : NJF * 4)];
-    uint4 dreg[kRows16 ? NT : 1][kRows16 ? NJ : 1];
+    // each tile's dm chunks (level 0: w_0 dout), kept for dv
+    float mreg[NT][FINEST ? NJ * E : NJF * 4];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         if (t >= ntile) break;                                // uniform
@@ -963,26 +908,17 @@ __global__ __launch_bounds__(64) void bwd_key_kernel(BwdLevelArgs a)
         float4_t ax = {0.f, 0.f, 0.f, 0.f}, ag = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            if constexpr (kBf16) {
-                ax = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kA[j]),
-                                                             __builtin_bit_cast(bf16x8_t, qB[j]), ax, 0, 0, 0);
-            } else {
-                ax = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kA[j].x), __uint_as_float(qB[j].x), ax, 0, 0, 0);
-                ax = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kA[j].y), __uint_as_float(qB[j].y), ax, 0, 0, 0);
-                ax = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kA[j].z), __uint_as_float(qB[j].z), ax, 0, 0, 0);
-                ax = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kA[j].w), __uint_as_float(qB[j].w), ax, 0, 0, 0);
-            }
-            // the query row for dk (fp32, or bf16 as stored)
-            if constexpr (kBf16) {
-                *reinterpret_cast<uint4*>(Rs16 + s * lay.qpitch + (g + 4 * j) * E) = qB[j];
-            } else {
-                float qf[E];
-                S::unpack(qB[j], qf);
-                float* qd = Rs + s * lay.qpitch + (g + 4 * j) * E;
+            ax = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kA[j].x), __uint_as_float(qB[j].x), ax, 0, 0, 0);
+            ax = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kA[j].y), __uint_as_float(qB[j].y), ax, 0, 0, 0);
+            ax = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kA[j].z), __uint_as_float(qB[j].z), ax, 0, 0, 0);
+            ax = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kA[j].w), __uint_as_float(qB[j].w), ax, 0, 0, 0);
+            // the query row for dk
+            float qf[E];
+            S::unpack(qB[j], qf);
+            float* qd = Rs + s * lay.pitch + (g + 4 * j) * E;
 #pragma unroll
-                for (int e4 = 0; e4 < E; e4 += 4)
-                    *reinterpret_cast<float4*>(qd + e4) = make_float4(qf[e4], qf[e4 + 1], qf[e4 + 2], qf[e4 + 3]);
-            }
+            for (int e4 = 0; e4 < E; e4 += 4)
+                *reinterpret_cast<float4*>(qd + e4) = make_float4(qf[e4], qf[e4 + 1], qf[e4 + 2], qf[e4 + 3]);
         }
         if constexpr (FINEST) {
             // <dout, v> on the storage type (times w_0 below), and w_0 dout in fp32 for dv
@@ -990,23 +926,14 @@ __global__ __launch_bounds__(64) void bwd_key_kernel(BwdLevelArgs a)
             for (int j = 0; j < NJ; ++j) {
                 const uint4 dd = masked4(load_at<uint4>(d_base, static_cast<uint32_t>(qtok) * static_cast<uint32_t>(C * TB) +
                                                                     (g + 4 * j) * 16), qm);
-                if constexpr (kBf16) {
-                    ag = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, vA[j]),
-                                                                 __builtin_bit_cast(bf16x8_t, dd), ag, 0, 0, 0);
-                } else {
-                    ag = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(vA[j].x), __uint_as_float(dd.x), ag, 0, 0, 0);
-                    ag = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(vA[j].y), __uint_as_float(dd.y), ag, 0, 0, 0);
-                    ag = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(vA[j].z), __uint_as_float(dd.z), ag, 0, 0, 0);
-                    ag = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(vA[j].w), __uint_as_float(dd.w), ag, 0, 0, 0);
-                }
-                if constexpr (kRows16) {
-                    dreg[t][j] = dd;
-                } else {
-                    float gf[E];
-                    S::unpack(dd, gf);
+                ag = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(vA[j].x), __uint_as_float(dd.x), ag, 0, 0, 0);
+                ag = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(vA[j].y), __uint_as_float(dd.y), ag, 0, 0, 0);
+                ag = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(vA[j].z), __uint_as_float(dd.z), ag, 0, 0, 0);
+                ag = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(vA[j].w), __uint_as_float(dd.w), ag, 0, 0, 0);
+                float gf[E];
+                S::unpack(dd, gf);
 #pragma unroll
-                    for (int e = 0; e < E; ++e) mreg[t][j * E + e] = w0 * gf[e];
-                }
+                for (int e = 0; e < E; ++e) mreg[t][j * E + e] = w0 * gf[e];
             }
         } else {
             // <dm, v> with dm in fp32, 4-channel chunks g, g+4, ...
@@ -1073,10 +1000,6 @@ __global__ __launch_bounds__(64) void bwd_key_kernel(BwdLevelArgs a)
                 vw[c] = kept ? 0.f : sc;
             }
         }
-        if constexpr (kRows16) {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) vw[c] *= w0;         // the dout rows are stored without w_0
-        }
         *reinterpret_cast<float4*>(dxs + s * 4) = make_float4(dx[0], dx[1], dx[2], dx[3]);
         vw_lane = make_float4(vw[0], vw[1], vw[2], vw[3]);
     }
@@ -1090,48 +1013,35 @@ __global__ __launch_bounds__(64) void bwd_key_kernel(BwdLevelArgs a)
     float4_t ok_ = {0.f, 0.f, 0.f, 0.f}, ov = {0.f, 0.f, 0.f, 0.f};
     for (int st = 0; st < sph; ++st) {
         const int sl = hh * sph + st;
-        ok_ = __builtin_amdgcn_mfma_f32_4x4x1f32(dxs[sl * 4 + t4], q_elem(sl, ch), ok_, 0, 0, 0);
+        ok_ = __builtin_amdgcn_mfma_f32_4x4x1f32(dxs[sl * 4 + t4], Rs[sl * lay.pitch + ch], ok_, 0, 0, 0);
     }
-    // the dm rows into the same buffer (lane 16g + n holds slot 16t + n's chunks g, g+4, ...), all
-    // slots at once or (kSplit) 32 at a time; slot sl of a pass is row sl - first
-    constexpr int kPasses = kSplit ? 2 : 1;
+    // the dm rows into the same buffer (lane 16g + n holds slot 16t + n's chunks g, g+4, ...)
+    wave_lds_sync();
+    *reinterpret_cast<float4*>(vws + lane * 4) = vw_lane;   // (vws aliases dxs)
 #pragma unroll
-    for (int pass = 0; pass < kPasses; ++pass) {
-        const int first = pass * lay.mslots;
-        if (first >= nsp) break;                              // uniform
-        wave_lds_sync();
-        if (pass == 0) *reinterpret_cast<float4*>(vws + lane * 4) = vw_lane;   // (vws aliases dxs)
+    for (int t = 0; t < NT; ++t) {
+        if (t >= ntile) break;                            // uniform
+        const int s = 16 * t + n16;
+        if constexpr (FINEST) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            if (t >= ntile) break;                            // uniform
-            if (16 * t < first || 16 * t >= first + lay.mslots) continue;   // uniform
-            const int s = 16 * t + n16 - first;
-            if constexpr (kRows16) {
+            for (int j = 0; j < NJ; ++j) {
+                float* md = Rs + s * lay.pitch + (g + 4 * j) * E;
 #pragma unroll
-                for (int j = 0; j < NJ; ++j) *reinterpret_cast<uint4*>(Rs16 + s * lay.mpitch + (g + 4 * j) * E) = dreg[t][j];
-            } else if constexpr (FINEST) {
-#pragma unroll
-                for (int j = 0; j < NJ; ++j) {
-                    float* md = Rs + s * lay.mpitch + (g + 4 * j) * E;
-#pragma unroll
-                    for (int e4 = 0; e4 < E; e4 += 4)
-                        *reinterpret_cast<float4*>(md + e4) = make_float4(mreg[t][j * E + e4], mreg[t][j * E + e4 + 1],
-                                                                          mreg[t][j * E + e4 + 2], mreg[t][j * E + e4 + 3]);
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < NJF; ++j)
-                    *reinterpret_cast<float4*>(Rs + s * lay.mpitch + (g + 4 * j) * 4) =
-                        make_float4(mreg[t][4 * j], mreg[t][4 * j + 1], mreg[t][4 * j + 2], mreg[t][4 * j + 3]);
+                for (int e4 = 0; e4 < E; e4 += 4)
+                    *reinterpret_cast<float4*>(md + e4) = make_float4(mreg[t][j * E + e4], mreg[t][j * E + e4 + 1],
+                                                                      mreg[t][j * E + e4 + 2], mreg[t][j * E + e4 + 3]);
             }
+        } else {
+#pragma unroll
+            for (int j = 0; j < NJF; ++j)
+                *reinterpret_cast<float4*>(Rs + s * lay.pitch + (g + 4 * j) * 4) =
+                    make_float4(mreg[t][4 * j], mreg[t][4 * j + 1], mreg[t][4 * j + 2], mreg[t][4 * j + 3]);
         }
-        wave_lds_sync();
-        const int cnt = min(nsp - first, lay.mslots);         // a multiple of 16
-        const int sphp = cnt / NH;
-        for (int st = 0; st < sphp; ++st) {
-            const int sl = hh * sphp + st;
-            ov = __builtin_amdgcn_mfma_f32_4x4x1f32(vws[(first + sl) * 4 + t4], m_elem(sl, ch), ov, 0, 0, 0);
-        }
+    }
+    wave_lds_sync();
+    for (int st = 0; st < sph; ++st) {
+        const int sl = hh * sph + st;
+        ov = __builtin_amdgcn_mfma_f32_4x4x1f32(vws[sl * 4 + t4], Rs[sl * lay.pitch + ch], ov, 0, 0, 0);
     }
     if constexpr (NH == 2) {
 #pragma unroll
@@ -1210,7 +1120,7 @@ template <typename T, int D, bool VA, bool FINEST>
 hipError_t launch_key_tdv(const BwdLevelArgs& a, long long max_chunks, hipStream_t stream)
 {
     if (max_chunks >= 0x7FFFFFFFLL) return hipErrorInvalidValue;
-    const size_t lds = key_lds<T, D, FINEST>().total;
+    const size_t lds = key_lds<D>().total;
     if (lds > device_max_lds()) return hipErrorInvalidValue;
     hipLaunchKernelGGL((bwd_key_kernel<T, D, VA, FINEST>), dim3(static_cast<unsigned>(max_chunks)), dim3(kWave), lds,
                        stream, a);

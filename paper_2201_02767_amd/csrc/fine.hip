@@ -1,8 +1,9 @@
 // Gathered fine attention at the finer levels: one wave per (parent query, head) work item, or per
 // pair of neighbouring parents on maps of one row; the per-item work (its independent loads in
 // item_head, then gather, MFMA logits, softmax, top-K, messages, the finest level's combination in
-// fine_item, both in fine_item.h; bf16 maps without a fused position encoding: fine_bf16.h). A workgroup holds up to four independent waves (fewer when a
-// wave's LDS region is large: 256 fp32 slots of d = 64); nothing synchronises across waves.
+// fine_item, both in fine_item.h; bf16 maps without a fused position encoding: fine_bf16.h). A
+// workgroup holds up to four independent waves (fewer when a wave's LDS region is large: 256 fp32
+// slots of d = 64); nothing synchronises across waves.
 #include "fine_bf16.h"
 #include "fine_item.h"
 
