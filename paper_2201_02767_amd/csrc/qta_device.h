@@ -267,17 +267,27 @@ __device__ __forceinline__ float wave_sum_fast(float x)
     return wave_allreduce(x, [](float a, float b) { return a + b; });
 }
 
+template <typename Op>
+__device__ __forceinline__ uint32_t wave_allreduce_u32(uint32_t x, Op op)
+{
+    x = op(x, __builtin_amdgcn_update_dpp(0u, x, kDppXor1, 0xF, 0xF, false));
+    x = op(x, __builtin_amdgcn_update_dpp(0u, x, kDppXor2, 0xF, 0xF, false));
+    x = op(x, __builtin_amdgcn_update_dpp(0u, x, kDppRowHalfMirror, 0xF, 0xF, false));
+    x = op(x, __builtin_amdgcn_update_dpp(0u, x, kDppRowMirror, 0xF, 0xF, false));
+    const auto r16 = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = op(r16[0], r16[1]);
+    const auto r32 = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return op(r32[0], r32[1]);
+}
+
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t x)
 {
-    auto mn = [](uint32_t a, uint32_t b) { return a < b ? a : b; };
-    x = mn(x, __builtin_amdgcn_update_dpp(0u, x, kDppXor1, 0xF, 0xF, false));
-    x = mn(x, __builtin_amdgcn_update_dpp(0u, x, kDppXor2, 0xF, 0xF, false));
-    x = mn(x, __builtin_amdgcn_update_dpp(0u, x, kDppRowHalfMirror, 0xF, 0xF, false));
-    x = mn(x, __builtin_amdgcn_update_dpp(0u, x, kDppRowMirror, 0xF, 0xF, false));
-    const auto r16 = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-    x = mn(r16[0], r16[1]);
-    const auto r32 = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-    return mn(r32[0], r32[1]);
+    return wave_allreduce_u32(x, [](uint32_t a, uint32_t b) { return a < b ? a : b; });
+}
+
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x)
+{
+    return wave_allreduce_u32(x, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
 }
 
 // Number of set bits of `mask` below this lane.

@@ -4,17 +4,21 @@
 // One wave per row, read once. Each lane holds NPER candidates of the row as 32-bit ranking keys (larger is
 // better, 0 = not a candidate):
 //   1. a lower bound of the K-th largest key: the K-th largest of the wave's group maxima (a lane's
-//      candidates form G groups; K groups have a member at or above it). A bitwise search on ballots over G
-//      values a lane instead of NPER;
+//      candidates form G groups; K groups have a member at or above it). Up to K = 8 by wave-wide maxima,
+//      else a bitwise search on ballots over G values a lane instead of NPER;
 //   2. the candidates at or above the bound (about K of them for K <= 16, 44 for K = 32 of one group a
 //      lane, 74 for K = 64 of four) go to LDS with their names. More than fit there (equal scores) are first
-//      cut to exactly K by the same search over all the wave's candidates;
-//   3. more than 64 survivors are cut to exactly K by the search over four a lane;
+//      cut to exactly K by the same search over all the wave's candidates, the lowest names at the cut first:
+//      those of the lowest columns, or with drawn names the lowest of those seen so far, a few chunks at a time;
+//   3. survivors are cut to exactly K where that costs less than placing them all;
 //   4. at most 64 survivors, one a lane: each counts the words (score, inverted name) above its own and,
 //      when fewer than K are, writes itself to that place. So the order is (score descending, name
 //      ascending), and repeated names stay separate candidates.
-// Bound by the row's read (3.3 of 5.1 TB/s at that size). The previous form took K rounds of a wave-wide 64-bit maximum over 1, 4, 16 or
-// 64 slots a lane: 9600 rows of 1200, K = 16: 226 -> 14.4 us.
+// What bounds it: for long rows their read (9600 rows of 1200, K = 16: 14.4 us, 3.3 of the 5.1 TB/s a copy
+// reaches), for short ones instruction issue. Rows of one score throughout, us a call (the host takes 10): 1e4 rows
+// of 100, K = 4 10 and K = 33 15; 5e3 of 200, K = 16 10; 244 of 4096, K = 4 10, with drawn names 22. With one
+// wave-wide 64-bit minimum for each place at the cut they took 24, 57, 22, 43 and 44; with K rounds of a maximum over
+// the whole row 10, 53, 17, 22 and 22 (and the long rows 226).
 #include "qta_device.h"
 #include "qta_internal.h"
 
@@ -23,6 +27,7 @@ namespace qta {
 namespace {
 
 constexpr int kSurvivors = 256;         // survivors of a row kept in LDS
+constexpr int kFew = 8;                 // K up to which the bound is found by maxima
 
 // Lists in LDS every one of the wave's keys above `thr`, with its name; returns how many.
 template <int NPER, typename Name>
@@ -43,36 +48,138 @@ __device__ __forceinline__ int list_above(const uint32_t (&key)[NPER], Name name
     return n;
 }
 
-// Lists exactly keff of the wave's keys: every key above the cut, and at the cut the lowest names first (of a
-// repeated name, the lowest place in the row), a wave-wide minimum for each.
-template <int NPER, typename Name>
-__device__ __forceinline__ void list_top(const uint32_t (&key)[NPER], Name name, int keff, uint32_t* lk, int32_t* ln)
+// wave_cut for a small keff: the largest value, the next, ... until keff keys reach it, a wave-wide maximum each.
+// Equal keys end it early, where the search by bits goes to the last bit.
+template <int NPER>
+__device__ __forceinline__ uint32_t wave_cut_few(const uint32_t (&key)[NPER], int keff)
 {
-    const uint32_t cut = wave_cut<NPER>(key, keff);
+    uint32_t cut = ~0u;
+    int n = 0;
+    do {                                                 // uniform
+        uint32_t top = 0u;
+#pragma unroll
+        for (int e = 0; e < NPER; ++e) top = max(top, key[e] < cut ? key[e] : 0u);
+        cut = wave_max_u32(top);
+        n = 0;
+#pragma unroll
+        for (int e = 0; e < NPER; ++e) n += __popcll(__ballot(key[e] >= cut));
+    } while (n < keff);
+    return cut;
+}
+
+// Leaves the `need` lowest of the m names at `ln` (need < m <= 64 S) there, in any order, and returns a bound: a
+// name whose complement is below it is none of them.
+template <int S>
+__device__ __forceinline__ uint32_t lowest_names(int32_t* ln, int m, int need)
+{
+    const int lane = threadIdx.x & 63;
+    uint32_t k[S];                                       // complements: the lowest names are the largest
+#pragma unroll
+    for (int e = 0; e < S; ++e) {
+        const int i = lane + kWave * e;
+        k[e] = i < m ? ~static_cast<uint32_t>(ln[i]) : 0u;
+    }
+    wave_lds_sync();
+    const uint32_t cut = need <= kFew ? wave_cut_few<S>(k, need) : wave_cut<S>(k, need);
+    int t = 0;
+#pragma unroll
+    for (int e = 0; e < 2 * S; ++e) {                    // those above the cut, then as many at it as are missing
+        const bool in = e < S ? k[e % S] > cut : k[e % S] == cut;
+        const uint64_t mask = __ballot(in);
+        const int pos = t + lanes_below(mask);
+        if (in && pos < need) ln[pos] = static_cast<int32_t>(~k[e % S]);
+        t += __popcll(mask);
+    }
+    wave_lds_sync();
+    return cut;
+}
+
+// Lists exactly keff of the wave's keys, of which at least keff reach `low`: every key above the cut, and at the cut
+// the lowest names first. Returns how many lie above the cut; the rest are for the caller where TIES is false.
+// ORDERED: names ascend with (e, lane), so those are the first in that order; else (at most kSurvivors keys in
+// all) the lowest names are found among the ties.
+template <int NPER, bool ORDERED, bool TIES, typename Name>
+__device__ __forceinline__ int list_top(const uint32_t (&key)[NPER], Name name, int keff, uint32_t low, uint32_t* lk,
+                                        int32_t* ln, uint32_t& cut)
+{
+    // mostly the bound itself is the cut: it was reached by too many keys because they are equal
     int n = 0;
 #pragma unroll
-    for (int e = 0; e < NPER; ++e) n += __popcll(__ballot(key[e] >= cut));
-    n = list_above<NPER>(key, name, n == keff ? cut - 1u : cut, lk, ln);
-    const uint32_t lane = threadIdx.x & 63;
-    uint64_t last = 0;                                   // (name, place in the row) + 1 of the last one taken
-    for (int r = n; r < keff; ++r) {                     // uniform
-        uint64_t mine = ~0ull;
+    for (int e = 0; e < NPER; ++e) n += __popcll(__ballot(key[e] > low));
+    cut = __builtin_amdgcn_readfirstlane(n) < keff ? low : wave_cut<NPER>(key, keff);
+    const int above = list_above<NPER>(key, name, cut, lk, ln), need = keff - above;
+    if constexpr (TIES) {
+        const int limit = ORDERED ? need : kSurvivors - above;
+        int m = 0;
 #pragma unroll
         for (int e = 0; e < NPER; ++e) {
-            const uint64_t w = (static_cast<uint64_t>(static_cast<uint32_t>(name(e))) << 32) | (lane + kWave * e);
-            if (key[e] == cut && w >= last && w < mine) mine = w;
+            if (m < limit) {                             // uniform
+                const uint64_t mask = __ballot(key[e] == cut);
+                const int pos = m + lanes_below(mask);
+                if (key[e] == cut && pos < limit) ln[above + pos] = name(e);
+                m += __popcll(mask);
+            }
         }
-        uint64_t low = mine;
-        for (int m = 32; m >= 1; m >>= 1) {
-            const uint64_t o = shfl_xor_u64(low, m);
-            low = o < low ? o : low;
-        }
-        if (lane == 0) {
-            lk[r] = cut;
-            ln[r] = static_cast<int32_t>(low >> 32);
-        }
-        last = low + 1;
+        wave_lds_sync();
+        if (!ORDERED && m > need && need > 0) lowest_names<NPER>(ln + above, m, need);        // uniform
+        if (static_cast<int>(threadIdx.x & 63) < need) lk[above + (threadIdx.x & 63)] = cut;
     }
+    return above;
+}
+
+// The `need` (at least 1) lowest names of the row's candidates with this ranking key to `ln`, which has room for
+// `cap` (at least 64 more than need) names. Keys and names are read again, a few chunks in flight, and names past the
+// `need` lowest so far are left out.
+__device__ __forceinline__ void list_ties(const float* keys, const int32_t* names, int n, uint32_t cut, int need, int cap,
+                                          int32_t* ln)
+{
+    constexpr int kBatch = 4;
+    const int lane = threadIdx.x & 63;
+    uint32_t floor = 0u;
+    int m = 0;
+    for (int j0 = 0; j0 < n; j0 += kBatch * kWave) {     // uniform
+        float k[kBatch];
+        int32_t nm[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int j = min(j0 + kWave * u + lane, n - 1);
+            k[u] = keys[j];
+            nm[u] = names[j];
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const bool in = j0 + kWave * u + lane < n && nm[u] >= 0 && ordered_bits(k[u]) == cut &&
+                            ~static_cast<uint32_t>(nm[u]) >= floor;
+            const uint64_t mask = __ballot(in);
+            if (m + __popcll(mask) > cap) {              // uniform
+                wave_lds_sync();
+                floor = lowest_names<kSurvivors / kWave>(ln, m, need);
+                m = need;
+            }
+            if (in) ln[m + lanes_below(mask)] = nm[u];
+            m += __popcll(mask);
+        }
+    }
+    wave_lds_sync();
+    if (m > need) lowest_names<kSurvivors / kWave>(ln, m, need);      // uniform
+}
+
+// Cuts the n listed survivors (at most 64 S, K < n) to exactly K, in place. ORDERED: listed by ascending name.
+template <int S, bool ORDERED>
+__device__ __forceinline__ void top_survivors(int n, int K, uint32_t low, uint32_t* lk, int32_t* ln)
+{
+    const int lane = threadIdx.x & 63;
+    uint32_t k[S], cut;
+    int32_t nm[S];
+#pragma unroll
+    for (int e = 0; e < S; ++e) {
+        const int i = lane + kWave * e;
+        k[e] = i < n ? lk[i] : 0u;
+        nm[e] = i < n ? ln[i] : -1;
+    }
+    wave_lds_sync();
+    list_top<S, ORDERED, true>(k, [&](int e) { return nm[e]; }, K, low, lk, ln, cut);
+    wave_lds_sync();
 }
 
 // NAMED: candidates are named by cand_idx (negative: not a candidate), else by their column.
@@ -127,7 +234,7 @@ __global__ __launch_bounds__(256) void topk_kernel(TopkArgs a)
             uint32_t m[1] = {gm[0]};
 #pragma unroll
             for (int g = 1; g < G; ++g) m[0] = max(m[0], gm[g]);
-            if (__popcll(__ballot(m[0] != 0u)) >= K) low = wave_cut<1>(m, K);
+            if (__popcll(__ballot(m[0] != 0u)) >= K) low = K <= kFew ? wave_cut_few<1>(m, K) : wave_cut<1>(m, K);
         }
         low = max(low, 1u);
     }
@@ -136,27 +243,29 @@ __global__ __launch_bounds__(256) void topk_kernel(TopkArgs a)
 #pragma unroll
     for (int e = 0; e < NPER; ++e) n += __popcll(__ballot(key[e] >= low));
     n = __builtin_amdgcn_readfirstlane(n);
-    if (n > kSurvivors) {                                // uniform; then n > K
-        list_top<NPER>(key, name, K, lkey[wave], lname[wave]);
+    if (NPER * kWave > kSurvivors && n > kSurvivors) {   // uniform; then n > K
+        uint32_t cut;
+        const int above = list_top<NPER, true, !NAMED>(key, name, K, low, lkey[wave], lname[wave], cut);
+        if (NAMED && above < K) {
+            list_ties(keys, names, a.n, cut, K - above, kSurvivors - above, lname[wave] + above);
+            if (lane < K - above) lkey[wave][above + lane] = cut;
+        }
         n = K;
     } else {
         list_above<NPER>(key, name, low - 1u, lkey[wave], lname[wave]);
     }
     wave_lds_sync();
-    // 3. at most 64 of them
-    if (n > kWave) {                                     // uniform
-        constexpr int S = kSurvivors / kWave;
-        uint32_t k4[S];
-        int32_t n4[S];
-#pragma unroll
-        for (int e = 0; e < S; ++e) {
-            const int i = lane + kWave * e;
-            k4[e] = i < n ? lkey[wave][i] : 0u;
-            n4[e] = i < n ? lname[wave][i] : -1;
-        }
-        wave_lds_sync();
-        list_top<S>(k4, [&](int e) { return n4[e]; }, K, lkey[wave], lname[wave]);
-        wave_lds_sync();
+    // 3. at most 64 of them, and not many more than K: placing one costs 8 instructions, cutting one a lane some 130,
+    // or 250 with drawn names and K > kFew (rows of 64 equal scores, K = 16: 31 us with that cut, 23 without)
+    if (n > K + 16) {                                    // uniform
+        bool cut = true;
+        if (NPER > 2 && n > 2 * kWave) top_survivors<kSurvivors / kWave, !NAMED>(n, K, low, lkey[wave], lname[wave]);
+        else if (NPER > 1 && n > kWave) top_survivors<2, !NAMED>(n, K, low, lkey[wave], lname[wave]);
+        else if (!NAMED || K <= kFew) top_survivors<1, !NAMED>(n, K, low, lkey[wave], lname[wave]);
+        else cut = false;
+        n = cut ? K : n;
+    } else if (n > kWave) {
+        top_survivors<2, !NAMED>(n, K, low, lkey[wave], lname[wave]);
         n = K;
     }
     // 4. each survivor's place (equal words, of a repeated name, in lane order)

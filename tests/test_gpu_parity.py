@@ -183,10 +183,31 @@ def test_topk_slots_and_survivors(dev, n, K):
     check_topk(dev, rng, keys, K)
 
 
-def check_topk(dev, rng, keys, K):
+@pytest.mark.parametrize("n", [40, 64, 100, 200, 256, 320, 700, 1200, 2000, 4096])
+@pytest.mark.parametrize("K", [1, 4, 8, 9, 20, 47, 64])
+def test_topk_ties_at_the_cut(dev, n, K):
+    """Far more equal scores at the cut than places: few values, one value under a few better ones (fewer than K,
+    and K of them), zeros and ones; names ascending, descending (each one lower than all before), drawn with
+    repeats, and one name throughout; exact."""
+    rng = np.random.default_rng(n + K)
+    keys = np.zeros((6, n), np.float32)
+    keys[0] = rng.integers(0, 5, n)
+    keys[1] = 0.5
+    keys[1, rng.permutation(n)[:K // 2]] = 1 + rng.random(min(K // 2, n))
+    keys[2, rng.permutation(n)[:K]] = 1 + rng.random(min(K, n))
+    keys[3] = rng.random(n) < 0.5
+    keys[4] = -np.inf
+    keys[5] = np.where(np.arange(n) % 64 < 3, 2.0, rng.standard_normal(n).round(1))    # the best in a few lanes
+    up = np.broadcast_to(np.arange(n, dtype=np.int32), keys.shape)
+    for names in (up, up[:, ::-1], rng.integers(0, n, keys.shape).astype(np.int32), np.full(keys.shape, 7, np.int32)):
+        check_topk(dev, rng, keys, K, np.ascontiguousarray(names))
+
+
+def check_topk(dev, rng, keys, K, names=None):
     rows, n = keys.shape
-    names = rng.permutation(rows * n).reshape(rows, n).astype(np.int32) % (3 * n)
-    names[rng.random((rows, n)) < 0.2] = -1                                    # non-candidates
+    if names is None:
+        names = rng.permutation(rows * n).reshape(rows, n).astype(np.int32) % (3 * n)
+        names[rng.random((rows, n)) < 0.2] = -1                                # non-candidates
     announce(f"topk rows={rows} n={n} K={K}")
     for cand in (None, names):
         idx, key = P.topk(torch.from_numpy(keys).to(dev), K,
