@@ -29,6 +29,9 @@ namespace {
 constexpr int kSurvivors = 256;         // survivors of a row kept in LDS
 constexpr int kFew = 8;                 // K up to which the bound is found by maxima
 
+// A candidate's ranking key: never 0, which the NaN of all one bits alone would get.
+__device__ __forceinline__ uint32_t rank_key(float f) { return max(ordered_bits(f), 1u); }
+
 // Lists in LDS every one of the wave's keys above `thr`, with its name; returns how many.
 template <int NPER, typename Name>
 __device__ __forceinline__ int list_above(const uint32_t (&key)[NPER], Name name, uint32_t thr, uint32_t* lk, int32_t* ln)
@@ -148,7 +151,7 @@ __device__ __forceinline__ void list_ties(const float* keys, const int32_t* name
         }
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
-            const bool in = j0 + kWave * u + lane < n && nm[u] >= 0 && ordered_bits(k[u]) == cut &&
+            const bool in = j0 + kWave * u + lane < n && nm[u] >= 0 && rank_key(k[u]) == cut &&
                             ~static_cast<uint32_t>(nm[u]) >= floor;
             const uint64_t mask = __ballot(in);
             if (m + __popcll(mask) > cap) {              // uniform
@@ -211,7 +214,7 @@ __global__ __launch_bounds__(256) void topk_kernel(TopkArgs a)
 #pragma unroll
         for (int e = 0; e < NPER; ++e) {
             const bool live = lane + kWave * e < a.n && (!NAMED || nm[NAMED ? e : 0] >= 0);
-            key[e] = live ? ordered_bits(__uint_as_float(key[e])) : 0u;
+            key[e] = live ? rank_key(__uint_as_float(key[e])) : 0u;
         }
     }
     asm volatile("" ::: "memory");       // names are read again where they are listed, not kept in registers

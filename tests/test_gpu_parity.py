@@ -203,6 +203,20 @@ def test_topk_ties_at_the_cut(dev, n, K):
         check_topk(dev, rng, keys, K, np.ascontiguousarray(names))
 
 
+@pytest.mark.parametrize("n", [50, 300])
+@pytest.mark.parametrize("bits", [0xFFFFFFFF, 0xFFC00000])
+def test_topk_keeps_a_negative_nan_as_the_lowest_candidate(dev, n, bits):
+    """A score that is a NaN with its sign set ranks below every number but stays a candidate: it fills a place
+    that no number does."""
+    keys = np.full((2, n), bits, np.uint32).view(np.float32)
+    keys[0, ::9] = np.arange(len(keys[0, ::9]))
+    best = np.arange(n)[::9][::-1].tolist()
+    idx, key = P.topk(torch.from_numpy(keys).to(dev), 50)
+    rest = [j for j in range(n) if j % 9][:50 - len(best)]
+    assert to_np(idx)[0].tolist() == best + rest and np.isnan(to_np(key)[0, len(best):]).all()
+    assert to_np(idx)[1].tolist() == list(range(50)) and np.isnan(to_np(key)[1]).all()
+
+
 def check_topk(dev, rng, keys, K, names=None):
     rows, n = keys.shape
     if names is None:
