@@ -20,6 +20,7 @@
 // The coarsest map holds at most QTA_MAX_COARSE tokens, so a row fits in 16 registers per lane.
 // Maps of at most 64 tokens take coarse_small_kernel instead (one wave per query row).
 #include <type_traits>
+#include <utility>
 
 #include "bf16_tiles.h"
 #include "qta_internal.h"
@@ -60,11 +61,56 @@ __host__ __device__ inline int coarse_behind(int N, int Q)
 // Waves per SIMD the kernel's registers must leave room for, so that two workgroups of 16 rows share a CU: up to
 // six values a lane everything fits 64 vector registers without a spill, and the figure also holds the scalar
 // registers under their limit, which the selection's masks would pass (bf16, d = 64, 400 workgroups of 196 keys:
-// 15.6 us without it, 12.4 with it). Not fp32 with d = 64 and five or six values, where 64 would spill, nor more.
+// 15.6 us without it, 12.4 with it). Not fp32 with d = 64 and five or six values, where 64 would spill, nor with
+// four, which fit without and are 2% slower with it, nor more.
 template <typename T, int D, int kPerLane>
 constexpr int coarse_waves()
 {
-    return kPerLane <= (sizeof(T) == 4 && D == 64 ? 4 : 6) ? 8 : 4;
+    return kPerLane <= (sizeof(T) == 4 && D == 64 ? 3 : 6) ? 8 : 4;
+}
+
+// The largest K for which phase 2 searches among the survivors of a bound (0: never). The bound costs a search of one
+// value a lane, and keeps out the less the larger K is: of 64 groups' maxima the K-th is reached by 18 keys for
+// K = 16, 44 for 32, 63 for 40, and more than 64 survivors fall back on all values. QuadTree-A also clears the
+// kept weights by a second pass over the values. Measured with the bound over without (16 and 64 maps, bf16; fp32
+// lies closer to 1): B, 15x17 keys: K = 8 0.97, 16 1.01; 18x21: 16 0.98, 24 1.02; 21x23: 16 0.89, 32 0.95, 44 1.03;
+// 28x27: 16 0.83, 40 0.98, 44 1.05; 29x31: 16 0.77, 32 0.93, 40 1.05. A: 15x17 K = 8 1.04; 18x21 K = 4 0.98;
+// 21x23 K = 8 0.97, 16 1.02; 28x27 K = 32 0.96; 31x33 K = 24 0.92, 32 1.02.
+template <typename T, int D, bool VA, int kPerLane>
+constexpr int bound_max_k()
+{
+    if (VA) return kPerLane >= 12 ? 32 : kPerLane == 8 ? 16 : kPerLane >= 5 ? 8 : 0;
+    // (fp32 with d = 64 and four values: the survivors' code takes it past the 64 registers of two workgroups)
+    if (kPerLane == 4) return sizeof(T) == 4 && D == 64 ? 0 : 12;
+    return kPerLane == 12 ? 40 : kPerLane >= 8 ? 32 : kPerLane >= 5 ? 20 : 0;
+}
+
+// x of another lane of the 16-lane row, R lanes on.
+template <int R>
+__device__ __forceinline__ uint32_t row_rotated(uint32_t x)
+{
+    if constexpr (R == 0) return x;
+    else return __builtin_amdgcn_update_dpp(0u, x, kDppRowRor + R, 0xF, 0xF, false);
+}
+
+// Whether a map's keys 64 on are its neighbours (at most two tokens away: maps 32 and 63 to 65 wide). A lane's keys
+// are then alike in a smooth image, the best ones lie in few lanes, and a bound of the lanes' maxima is too low
+// (64 and 32 wide: 1.06 and 1.04 of the time without it at K = 20 and 28; with the groups below 1.0 and 0.99).
+inline bool lane_keys_near(int W)
+{
+    const int dy = (kWave + W / 2) / W, dx = kWave - dy * W;
+    return dx * dx + dy * dy <= 4;
+}
+
+// The largest key of each of 64 groups, one a lane: key e of every lane belongs to the group of another lane of its
+// row, which parts a map's columns where lane_keys_near.
+template <int... E>
+__device__ __forceinline__ uint32_t group_maxima(const uint32_t (&key)[sizeof...(E)], std::integer_sequence<int, E...>)
+{
+    constexpr int kRotation[16] = {0, 7, 3, 12, 9, 1, 14, 6, 11, 4, 15, 8, 2, 13, 5, 10};    // no common step
+    uint32_t top = 0u;
+    ((top = max(top, row_rotated<kRotation[E]>(key[E]))), ...);
+    return top;
 }
 
 template <typename T, int D, bool VA, int kPerLane, int Q>
@@ -237,23 +283,29 @@ __global__ __launch_bounds__(Q * kWave) __attribute__((amdgpu_waves_per_eu(coars
             const int keff = a.K < N ? a.K : N;
             int32_t* const so = a.sel_idx + ((static_cast<size_t>(b) * a.heads + h) * N + qi) * a.K;
             float* const ko = a.sel_key + ((static_cast<size_t>(b) * a.heads + h) * N + qi) * a.K;
-            // With four or more values a lane (N > 64, so every lane holds a key): the K-th largest of the lanes'
-            // maxima bounds the K-th largest key from below, and the few keys at or above it go to LDS (the
-            // row's logits are in registers) in index order, one a lane. The searches then test one value a
-            // lane and bit, and the listing runs once instead of kPerLane times.
+            // Up to kBoundK (less where a lane's keys are alike; N > 64, so every group has a key): the K-th
+            // largest of 64 groups' maxima bounds the
+            // K-th largest key from below, and the few keys at or above it go to LDS (the row's logits are in
+            // registers) in index order, one a lane. The searches then test one value a lane and bit, and the
+            // listing runs once instead of kPerLane times.
+            constexpr int kBoundK = bound_max_k<T, D, VA, kPerLane>();
             int nsurv = kWave + 1;
             uint32_t low = 0u;
-            if constexpr (kPerLane >= 4) {
+            if (kBoundK > 0 && keff <= (a.near ? kBoundK * 3 / 4 : kBoundK)) {       // uniform
                 uint32_t top[1] = {0u};
+                if (a.near) {
+                    top[0] = group_maxima(key, std::make_integer_sequence<int, kPerLane>());
+                } else {
 #pragma unroll
-                for (int e = 0; e < kPerLane; ++e) top[0] = max(top[0], key[e]);
+                    for (int e = 0; e < kPerLane; ++e) top[0] = max(top[0], key[e]);
+                }
                 low = wave_cut<1>(top, keff);
                 nsurv = 0;
 #pragma unroll
                 for (int e = 0; e < kPerLane; ++e) nsurv += __popcll(__ballot(key[e] >= low));
                 nsurv = __builtin_amdgcn_readfirstlane(nsurv);
             }
-            if (kPerLane >= 4 && nsurv <= kWave) {           // uniform; more only where many keys are equal
+            if (kBoundK > 0 && nsurv <= kWave) {             // uniform
                 int before = 0;
 #pragma unroll
                 for (int e = 0; e < kPerLane; ++e) {
@@ -725,8 +777,10 @@ hipError_t launch_per_lane(const CoarseArgs& a, hipStream_t stream)
 
 }  // namespace
 
-hipError_t launch_coarse_attn(const CoarseArgs& a, int d, bool variant_a, bool bf16_in, hipStream_t stream)
+hipError_t launch_coarse_attn(const CoarseArgs& args, int d, bool variant_a, bool bf16_in, hipStream_t stream)
 {
+    CoarseArgs a = args;
+    a.near = a.Wc > 0 && lane_keys_near(a.Wc);
 #define QTA_COARSE_CASE(T, D)                                                                     \
     if (d == D) return variant_a ? launch_per_lane<T, D, true>(a, stream) : launch_per_lane<T, D, false>(a, stream);
     if (bf16_in) {

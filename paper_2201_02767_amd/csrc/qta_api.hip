@@ -411,6 +411,7 @@ qta_status qta_coarse_attn(const void* qc, const void* kc, const void* vc, int B
     a.B = B;
     a.heads = heads;
     a.N = Hc * Wc;
+    a.Wc = Wc;
     a.C = heads * d;
     a.K = sel_idx ? K : 0;
     a.scale = resolve_scale(scale, d);

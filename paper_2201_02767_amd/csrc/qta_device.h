@@ -144,6 +144,7 @@ constexpr int kDppXor1 = 0xB1;         // quad_perm [1,0,3,2]
 constexpr int kDppXor2 = 0x4E;         // quad_perm [2,3,0,1]
 constexpr int kDppRowShl4 = 0x104;
 constexpr int kDppRowShr4 = 0x114;
+constexpr int kDppRowRor = 0x120;      // + n, 1 <= n <= 15: within a 16-lane row, from n lanes away, cyclically
 constexpr int kDppRowRor4 = 0x124;     // within a 16-lane row: lane (lane + 4) mod 16
 constexpr int kDppRowRor8 = 0x128;     // within a 16-lane row: lane ^ 8
 constexpr int kDppRowMirror = 0x140;   // within a row: lane -> 15 - lane

@@ -120,8 +120,9 @@ struct CoarseArgs {
     const float* pe_w;          // or, fused (coarse_attn_kernel): this level's depth-wise kernels fp32 [C][3][3],
                                 // applied to v around each query (an Hc x Wc map) and added to m; or NULL
     const float* pe_b;          // its bias fp32 [C], or NULL
-    int Wc;                     // map width (with pe_w)
+    int Wc;                     // map width
     int levels;
+    bool near;                  // a lane's keys are near neighbours of the map; set by launch_coarse_attn
 };
 
 // Division of 0 <= n < 2^31 by a fixed divisor d >= 1 with one high multiply and a shift:

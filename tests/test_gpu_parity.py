@@ -398,13 +398,17 @@ def test_largest_coarse_level(dev, dtype):
                                                    ("B", 3, 43, 2, 32, 64), ("A", 11, 19, 1, 32, 64),
                                                    ("B", 14, 14, 1, 64, 8), ("B", 12, 25, 1, 32, 16),
                                                    ("A", 16, 24, 1, 32, 32), ("B", 7, 55, 1, 64, 8),
-                                                   ("A", 19, 27, 1, 64, 16), ("B", 31, 33, 1, 64, 64)])
+                                                   ("A", 19, 27, 1, 64, 16), ("B", 31, 33, 1, 64, 64),
+                                                   ("B", 16, 32, 1, 32, 32), ("B", 16, 64, 1, 64, 33),
+                                                   ("A", 8, 64, 1, 32, 8), ("A", 20, 32, 1, 64, 32),
+                                                   ("B", 24, 28, 1, 32, 40), ("A", 18, 19, 1, 32, 9),
+                                                   ("B", 16, 16, 1, 32, 12), ("B", 9, 32, 1, 64, 20)])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("equal", [0.0, 0.15, 1.0])
 def test_coarse_rows_and_survivors(dev, variant, h, w, heads, d, K, dtype, equal):
     """Coarsest maps at the edges of the values a lane holds, of the 64-key value chunks and of the K of a bound's
-    survivors; with distinct keys, with a sixth of the cells equal (ties at the cut) and all equal (more
-    survivors than a wave has lanes). The tolerance is the parity protocol's."""
+    survivors, and maps whose columns are a lane's; with distinct keys, with a sixth of the cells equal (ties at
+    the cut) and all equal (more survivors than a wave has lanes). The tolerance is the parity protocol's."""
     rng = np.random.default_rng(h * w + K)
     q, k, v = rand_qkv(31 + h * w, 1, 2 * h, 2 * w, heads, d, dtype, scale=0.7)
     same = np.repeat(np.repeat(rng.random((h, w)) < equal, 2, 0), 2, 1)
