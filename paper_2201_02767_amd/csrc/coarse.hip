@@ -719,15 +719,17 @@ hipError_t launch_small(const CoarseArgs& a, hipStream_t stream)
 // phase). Fewer rows per workgroup spread a small map's rows over more compute units, so that the
 // selection's scalar work and each phase's latency are shared by fewer rows, at the price of more
 // passes over the map's keys and values (from L2) and of MFMA tiles only half filled. Measured on
-// MI355X (bf16, 8 against 16 rows): d = 32, 16 maps of 300 keys 11.6 and 12.6 us, 128 of them 46.1
-// and 48.7, 8 maps of 100 5.2 and 6.3; 16 maps of 512 11.9 and 10.8 but 64 of them 52.2 and 59.2; 16 of
-// 1023 48.1 and 44.6; d = 64, 32 maps of 196 13.3 and 12.3, 16 of 1023 63.3 and 56.5. So 8 rows for bf16 with d = 32
-// (one 16-byte chunk per key row and k-step pair) and small maps, 16 elsewhere: fp32, d = 64, and from 385 keys,
-// where the passes over the keys count for more.
+// MI355X, a call of the stage, bf16, d = 32, K = 16, 8 against 16 rows: 16 maps of 300 keys 11.6 and 12.6 us, 128 of
+// them 46.1 and 48.7 (both without the ordering launch); 4, 16, 64 and 128 maps of 440 keys 10.3 and 11.5, 20.2 and
+// 20.4, 55 and 61, 95 and 117; of 512 11.1 and 11.8, 22.2 and 22.3, 66 and 73, 118 and 140; of 672 14.3 and 13.3, 36.1
+// and 33.4, 113 and 110, 218 and 209; of 1023 17.6 and 15.8, 56 and 51, 200 and 194, 394 and 383 (8 rows are ahead
+// there for K = 64 alone). d = 64, 32 maps of 196 keys: 13.3 and 12.3. So 8 rows for bf16 with d = 32 (one 16-byte
+// chunk per key row and k-step pair) up to 512 keys, 16 elsewhere: fp32, d = 64, and more keys, where the passes over
+// them count for more.
 template <typename T, int D, int kPerLane>
 constexpr int coarse_rows()
 {
-    return (sizeof(T) == 2 && D == 32 && kPerLane < 8) ? 8 : 16;
+    return (sizeof(T) == 2 && D == 32 && kPerLane <= 8) ? 8 : 16;
 }
 
 template <typename T, int D, bool VA, int kPerLane, int Q>
