@@ -164,12 +164,17 @@ __device__ __forceinline__ void item(const FineArgs& a, const int it, unsigned c
     };
     load_keys(0);
     const __amdgpu_buffer_rsrc_t vres = map_resource(vg);
-    // value rows into LDS: one instruction lands its lanes' chunks in lane order
+    // value rows into LDS: one instruction lands its lanes' chunks in lane order. The last quarter of 16 tiles holds no
+    // slot up to K = 48; QuadTree-A leaves it out (zeros): 160x224 maps, 2 x 32, K = 36 120 -> 115 us (the general
+    // kernel, nine tiles of 16: 116), K = 64 133 -> 131; B would gain 3% there and lose 2% at K = 64
+    auto tile_live = [&](int t) { return !VA || NT < 16 || t < 12 || nslot > 192; };       // uniform
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
-            load_lds16(vres, off[t], 64 * j, vlds + t * TS + j * 1024);
+        for (int j = 0; j < NJ; ++j) {
+            if (tile_live(t)) load_lds16(vres, off[t], 64 * j, vlds + t * TS + j * 1024);
+            else *(lds_ptr<u32x4_t>)(vlds + t * TS + j * 1024 + lane * 16) = u32x4_t{0u, 0u, 0u, 0u};
+        }
 
     // ---- the finest level's combination inputs. Lane 16g + n ends with query g's message at channels
     //      16 ct + n. out = w_0 m + sum over the ancestors e of w_e anc_e is a product of a 4 x E by an E x D
@@ -221,6 +226,11 @@ __device__ __forceinline__ void item(const FineArgs& a, const int it, unsigned c
     float xt[NT];
 #pragma unroll
     for (int t0 = 0; t0 < NT; t0 += kTB) {
+        if (!tile_live(t0)) {                                    // uniform
+#pragma unroll
+            for (int i = 0; i < kTB; ++i) xt[t0 + i] = 0.f;      // (masked below)
+            continue;
+        }
         if (t0 > 0) load_keys(t0);
 #pragma unroll
         for (int i = 0; i < kTB; ++i) {

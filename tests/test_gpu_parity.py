@@ -363,6 +363,8 @@ def test_forward_parity(dev, variant, dtype, B, H, W, heads, d, L, K):
     (1, 21, 26, 3, 64, 3, 9, False),       # four tiles, d = 64
     (1, 33, 31, 2, 32, 6, 17, False),      # eight tiles; five ancestors (two groups), odd at every level
     (1, 22, 25, 1, 64, 3, 33, False),      # sixteen tiles, d = 64
+    (1, 35, 31, 1, 32, 3, 48, False),      # sixteen tiles, the last four without a slot
+    (1, 31, 35, 1, 32, 3, 49, False),      # and with one
     (2, 3, 45, 2, 32, 6, 6, True),         # one-row maps, pairs of parents with a half-empty last pair
     (1, 2, 37, 1, 64, 5, 20, True),        # the same with eight tiles and five ancestors
 ])
