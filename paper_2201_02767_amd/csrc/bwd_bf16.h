@@ -175,7 +175,9 @@ __device__ __forceinline__ void query_item(const BwdLevelArgs& a, const int it, 
         flat = __mul24(cy, W) + cx;
         const bool ok = own < 4 * K && J >= 0 && cy < H && cx < W;
         uint32_t o = kvb ? static_cast<uint32_t>(Jc * 4 + (own & 3)) * RB : __umul24(static_cast<uint32_t>(flat), tok_bytes);
-        o = ok ? o : 0u;                                      // a missing candidate reads the map's first row
+        // a missing candidate reads the row of slot 0, always a candidate's (see fine_bf16.h)
+        const uint32_t first = __builtin_amdgcn_readfirstlane(o);
+        o = ok ? o : first;
         flat = ok ? flat : -1;
         okm = __ballot(ok);
         quad_offsets<NT>(o, gather_chunk(lane), off);

@@ -5,7 +5,7 @@
 // Work item = one parent query at level l+1 and one head (ROW: two neighbouring parents of a one-row
 // map); one wave owns it. Candidate slot s = 4r + c is child c of kept key r (ROW: s = 2(half*K + r) + c).
 // The slots are taken in NT tiles of 16, NT = 1, 2, 4, 8 or 16 (a power of two that covers 4K; slots past
-// 4K read the map's first row and weigh nothing).
+// 4K read slot 0's row and weigh nothing).
 //   1. lane 4n + t works out the address of slot 16t + n (and of the slots 64 on) once and hands it to its
 //      quad, which gathers that slot's row: the key rows into registers, the value rows straight into the
 //      wave's LDS (bf16_tiles.h);
@@ -131,6 +131,7 @@ __device__ __forceinline__ void item(const FineArgs& a, const int it, unsigned c
     uint64_t okm[SPL];                               // bit 4n + t: slot 64u + 16t + n is a candidate
     uint32_t off[NT];                                // tile t: this lane's chunk of slot 16t + (lane >> 2)
     const uint32_t chunk16 = gather_chunk(lane);
+    uint32_t first = 0u;                             // slot 0's row, always a candidate's
 #pragma unroll
     for (int u = 0; u < SPL; ++u) {
         const int s = 64 * u + own;
@@ -148,7 +149,10 @@ __device__ __forceinline__ void item(const FineArgs& a, const int it, unsigned c
             ok = s < nslot && J[u] >= 0 && cy < H && cx < W;
             o = kvb ? static_cast<uint32_t>(Jc * 4 + (s & 3)) * RB : __umul24(static_cast<uint32_t>(flat[u]), tok_bytes);
         }
-        o = ok ? o : 0u;                             // a missing candidate reads the map's first row
+        // a missing candidate reads slot 0's row: its weight is zero, and zero times a row that the queries attend
+        // anyway takes an infinity or a NaN nowhere else
+        if (u == 0) first = __builtin_amdgcn_readfirstlane(o);
+        o = ok ? o : first;
         flat[u] = ok ? flat[u] : -1;
         okm[u] = __ballot(ok);
         quad_offsets<(NT < 4 ? NT : 4)>(o, chunk16, off + 4 * u);

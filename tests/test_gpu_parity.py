@@ -377,6 +377,27 @@ def test_bf16_slot_tiles_and_ancestors(dev, variant, weighted, B, H, W, heads, d
 
 
 @pytest.mark.parametrize("variant", ["A", "B"])
+@pytest.mark.parametrize("H,W,d,K", [(15, 14, 32, 5), (19, 21, 64, 5), (16, 18, 64, 2), (22, 21, 64, 20)])
+def test_an_infinite_value_reaches_only_the_queries_that_attend_it(dev, variant, H, W, d, K):
+    """Value levels are the caller's, and the first token of level 0 holds infinities: queries whose parent kept
+    that token's parent get no finite message, and all others exactly what finite values give them, also where
+    slots hold no candidate (K that fills no tile, children off an odd map)."""
+    q, k, v = (dev_t(x, "bf16", dev) for x in rand_qkv(H * W + K, 1, H, W, 2, d, "bf16"))
+    Hc, Wc = (H + 1) // 2, (W + 1) // 2
+    v1 = torch.randn(1, Hc, Wc, 2, d, device=dev).bfloat16()
+    plan = P.Plan(1, H, W, 2, d, levels=2, K=K, variant=variant, dtype=torch.bfloat16, device=dev, v_supplied=True)
+    ref = plan.run(q, k, v, v_levels=[None, v1]).clone()
+    v[0, 0, 0] = float("inf")
+    out = plan.run(q, k, v, v_levels=[None, v1])
+    torch.cuda.synchronize()
+    hit = (plan.selection(1)[0] == 0).any(-1).reshape(1, 2, Hc, Wc)                    # parents that kept token 0's
+    hit = hit.repeat_interleave(2, 2).repeat_interleave(2, 3)[:, :, :H, :W].permute(0, 2, 3, 1)
+    assert bool(hit.any()) and not bool(hit.all())
+    assert not bool(out[hit].isfinite().any())
+    assert torch.equal(out[~hit], ref[~hit])
+
+
+@pytest.mark.parametrize("variant", ["A", "B"])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_single_level_is_dense_attention(dev, variant, dtype):
     B, H, W, heads, d = 2, 9, 11, 2, 32
