@@ -294,6 +294,9 @@ __device__ __forceinline__ void item(const FineArgs& a, const int it, unsigned c
 
     // ---- 5a. the weights into LDS: [query g][place of n16][t] ----
     store_weights<NT>(plds, wt, lane);
+    // (A's selection below clears single weights among them through another type, which alone would not keep the
+    // compiler from moving these stores past those)
+    if constexpr (VA && !FINEST) asm volatile("" ::: "memory");
 
     // ---- 4. this level's selection (levels above the finest): each query keeps its Ks best candidates ----
     if constexpr (!FINEST) {
