@@ -145,6 +145,8 @@ def run_backward(dev, q, k, v, g, *, levels, K, variant, dtype, w=None, scale=No
     ("B", "f32", 1, 257, 200, 1, 32, 9, 2, True),      # nine levels, coarsest 2x1 (its 16-level kernel)
     ("A", "bf16", 1, 27, 33, 2, 32, 3, [0, 2, 16], False),   # K schedule, blocked level 1
     ("B", "f32", 1, 33, 29, 2, 32, 4, [0, 8, 4, 2], True),
+    ("B", "bf16", 1, 33, 29, 2, 32, 4, [0, 3, 9, 2], True),  # K schedule, coarse to fine
+    ("B", "bf16", 1, 27, 34, 1, 64, 3, [0, 16, 4], False),
 ])
 def test_backward_matches_oracle(dev, variant, dtype, B, H, W, heads, d, L, K, with_w):
     seed = 300 + H * W + L
@@ -169,7 +171,30 @@ def test_backward_bf16_tiles(dev, variant, B, H, W, heads, d, L, K):
     if K == 2:
         k[:, : H // 8] *= 2         # a few keys draw most queries
     w = np.random.default_rng(seed).random((B, H * W, heads, L)).astype(np.float32) if variant == "B" else None
-    run_backward(dev, q, k, v, g, levels=L, K=K, variant=variant, dtype="bf16", w=w, label="tiles")
+    plan, _, _ = run_backward(dev, q, k, v, g, levels=L, K=K, variant=variant, dtype="bf16", w=w, label="tiles")
+    if K == 2:
+        assert longest_list(plan) > 32
+
+
+def longest_list(plan):
+    """The most parents of one map and head that keep one level-1 key (lists beyond 32 are summed from parts)."""
+    idx, _ = plan.selection(1)
+    return max(int(torch.bincount(row[row >= 0]).max()) for row in idx.flatten(0, 1).flatten(1))
+
+
+@pytest.mark.parametrize("variant", ["A", "B"])
+@pytest.mark.parametrize("W,heads,d,L,K", [
+    (37, 1, 64, 3, 4),              # four parents a wave in the combination's backward, a run cut short
+    (150, 1, 64, 6, 3),             # and levels its blocks do not hold, past the first four
+    (67, 3, 64, 5, 8),
+    (150, 2, 32, 6, 5),             # eight parents a wave
+    (259, 1, 32, 7, 2),
+])
+def test_backward_bf16_one_row_maps(dev, variant, W, heads, d, L, K):
+    """One-row bf16 maps of several depths, against the oracle like the rest."""
+    q, k, v, g = (rand(500 + W + i, (2, 3, W, heads, d), "bf16") for i in range(4))
+    w = np.random.default_rng(W).random((2, 3 * W, heads, L)).astype(np.float32) if variant == "B" else None
+    run_backward(dev, q, k, v, g, levels=L, K=K, variant=variant, dtype="bf16", w=w, epipolar=True, label="rows")
 
 
 @pytest.mark.parametrize("variant,dtype", [("A", "bf16"), ("B", "f32")])
@@ -328,8 +353,34 @@ def test_autograd_bf16_gradients_are_the_backwards_rounded(dev, variant, B, H, W
     leaves = [t.clone().requires_grad_(True) for t in (q, k, v)]
     out = P.attention(*leaves, levels=L, K=5, variant=variant, w=w, plan=plan, epipolar=epipolar)
     got = torch.autograd.grad(out, leaves, g)
+    check_rounded(got, ref)
+
+
+def check_rounded(got, ref):
     for a, r in zip(got, ref):
         assert a.dtype == torch.bfloat16 and a.shape == r.shape
         diff = (a.float() - r).abs()
         assert bool((diff <= r.abs() * 2.0 ** -7 + 1e-6 * r.abs().max()).all())
         assert float((a != r.bfloat16()).float().mean()) < 1e-2
+
+
+@pytest.mark.parametrize("H,W,heads,d", [(70, 90, 1, 32), (70, 90, 1, 64), (67, 89, 2, 32)])
+@pytest.mark.parametrize("side_stream", [False, True])
+def test_autograd_bf16_gradients_of_long_key_lists(dev, H, W, heads, d, side_stream):
+    """The same where keys are kept by many more parents than one part of the key pass takes (asserted), so
+    that their bf16 gradients come from the parts' sum; on the default stream and on another."""
+    q, k, v, g = (torch.from_numpy(rand(830 + i, (1, H, W, heads, d), "bf16")).to(dev).bfloat16() for i in range(4))
+    k[:, :H // 8] *= 2                  # a few keys draw most queries
+    w = torch.rand(1, H * W, heads, 3, device=dev)
+    plan = P.Plan(1, H, W, heads, d, levels=3, K=2, variant="B", dtype=torch.bfloat16, device=dev)
+    plan.run(q, k, v, w)
+    assert longest_list(plan) > 64
+    ref = [t.clone() for t in plan.backward(q, k, v, g, w)[:3]]
+    leaves = [t.clone().requires_grad_(True) for t in (q, k, v)]
+    stream = torch.cuda.Stream(dev) if side_stream else torch.cuda.current_stream(dev)
+    stream.wait_stream(torch.cuda.current_stream(dev))
+    with torch.cuda.stream(stream):
+        out = P.attention(*leaves, levels=3, K=2, variant="B", w=w, plan=plan)
+        got = torch.autograd.grad(out, leaves, g)
+    torch.cuda.current_stream(dev).wait_stream(stream)
+    check_rounded(got, ref)
