@@ -39,7 +39,8 @@ __device__ __forceinline__ uint32_t pack2(float lo, float hi)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2_t));
 }
 
-// x split into three bf16 terms: x = hi + mid + lo exactly (24 significant bits), two values a word.
+// x split into three bf16 terms: x = hi + mid + lo exactly (24 significant bits), two values a word. x finite, as
+// the entry points ask: an infinity, or a value that rounds to one in bf16 (3.39e38 on), gives NaN in the sums.
 struct Split2 {
     uint32_t hi, mid, lo;
 };
