@@ -1,9 +1,10 @@
 // Backward pass of QuadTree attention: gradients of q, k, v (and QuadTree-B's w) for an upstream
 // gradient of the output, with the kept-key sets of the forward held fixed (top-K is a selection,
 // not differentiated). The chain rule runs through the forward's steps in reverse (Sec. 3.2):
-//   1. combination (Eqs. 2, 5), inside the finest level's query pass: dm^l of a level-l token sums
-//      w_{i,l} dout_i over its finest descendants (each sibling group adds its four queries' share
-//      to its ancestors); dw_{i,l} = <dout_i, m^l of the ancestor>
+//   1. combination (Eqs. 2, 5), inside the finest level's query pass here, a pass of its own for bf16
+//      maps (bwd_bf16.h): dm^l of a level-l token sums w_{i,l} dout_i over its finest descendants
+//      (each sibling group adds its four queries' share to its ancestors); dw_{i,l} = <dout_i, m^l
+//      of the ancestor>
 //   2. each finer level, finest first, in two passes:
 //      query pass, one wave per sibling group as in the forward: the logits and <dm, v> of every
 //      candidate on MFMA, the softmax gradient (B: over the candidates, Eq. 6; A: over each kept
@@ -22,9 +23,10 @@
 //   4. pyramids: a pooled token hands 1/n of its gradient to each of its n valid children; the
 //      level-0 gradients add every ancestor's, scaled along the chain      (bwd_unpool_kernel)
 // The passes of 2 are written here for fp32; bf16 maps take those of bwd_bf16.h, and the launchers below pick.
-// All gradients are fp32. The message gradients of levels >= 2 are summed with atomics and the
-// parents within one kept key's list come in the order the query pass's count atomics hand out, so
-// the last bits of the gradients may differ between runs.
+// Gradients are summed and handed on in fp32; bf16 results, where the caller asks for them, are rounded as the
+// finest level's passes store them (QuadTree-B) or by the unpooling. The message gradients of levels >= 2 (bf16:
+// >= 3) are summed with atomics and the parents within one kept key's list come in the order the query pass's
+// count atomics hand out, so the last bits of the gradients may differ between runs.
 #include "qta_device.h"
 #include "qta_internal.h"
 
@@ -445,15 +447,10 @@ __device__ __forceinline__ void bwd_item(const BwdLevelArgs& a, const int item, 
                     }
                     // lane 16g + e stores element e of chunk g + 4j (one instruction covers the head's
                     // channels contiguously): the sum over the four queries (query n16 >> 2, on lanes
-                    // 4 apart). Lane 4q + i contributes its query's elements i (and, with eight per
-                    // chunk, i + 4); after the sums over lanes 4 apart, lanes 0-3 hold elements 0-3
-                    // and lanes 4-7 elements 4-7
+                    // 4 apart). Lane 4q + i contributes its query's element i; after the sum over lanes
+                    // 4 apart, lanes 0-3 hold elements 0-3
                     const int ei = n16 & 3;
-                    float mine = row_sum_stride4(wl[i] * pick4_at(gv[j], 0, ei));
-                    if constexpr (E == 8) {
-                        const float hi = row_sum_stride4(wl[i] * pick4_at(gv[j], 4, ei));
-                        mine = n16 < 4 ? mine : hi;
-                    }
+                    const float mine = row_sum_stride4(wl[i] * pick4_at(gv[j], 0, ei));
                     if (n16 < E) {
                         float* dst = a.dm_out[lv] + arow[i] + c0 + n16;
                         if (lv == 1)

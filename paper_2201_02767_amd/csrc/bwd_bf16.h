@@ -354,20 +354,6 @@ __device__ __forceinline__ float add_across(float x)
     }
 }
 
-// The sum over each aligned group of G = 8 or 16 lanes, in all of them.
-template <int G>
-__device__ __forceinline__ float add_group(float x)
-{
-    auto step = [](float v, auto ctrl) {
-        return v + __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), decltype(ctrl)::value, 0xF, 0xF, false));
-    };
-    x = step(x, std::integral_constant<int, kDppXor1>());
-    x = step(x, std::integral_constant<int, kDppXor2>());
-    x = step(x, std::integral_constant<int, kDppRowHalfMirror>());
-    if constexpr (G == 16) x = step(x, std::integral_constant<int, kDppRowMirror>());
-    return x;
-}
-
 // dm^l of every level l >= 1 sums w_{i,l} dout_i over a token's level-0 descendants i, and dw_{i,l} =
 // <dout_i, m^l of the ancestor>. One wave takes one head of a block of neighbouring parents (level-1 tokens;
 // 4x2 with d = 32, 2x2 with d = 64, a run on one-row maps): lane Q i + e has channels 4e .. 4e+3 of parent i's
@@ -467,7 +453,7 @@ __device__ __forceinline__ void combine_item(const BwdLevelArgs& a, const Combin
             if (want_dw) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
-                    part[q][j] = add_group<Q>(g[q][0] * m[j][0] + g[q][1] * m[j][1] + g[q][2] * m[j][2] + g[q][3] * m[j][3]);
+                    part[q][j] = group_sum<Q>(g[q][0] * m[j][0] + g[q][1] * m[j][1] + g[q][2] * m[j][2] + g[q][3] * m[j][3]);
             }
             // over the block's parents that share the level-l ancestor
             int bits = 0;                                     // of i, summed over

@@ -237,17 +237,17 @@ __global__ __launch_bounds__(Q * kWave) __attribute__((amdgpu_waves_per_eu(coars
     // the order in which a transposed read (bf16_tiles.h) hands lane group g keys 32u + 8g .. 32u + 8g + 7,
     // which are consecutive in a logit row.
     const int nchunk = (N + kWave - 1) / kWave;
-    auto load_values = [&](int c, int jj) {
+    auto load_values = [&](int jj) {
         if constexpr (kBf16) {
             const __amdgpu_buffer_rsrc_t vres = tiles::map_resource(vmap);
-            const int n = lane >> 2, key0 = c * kWave + 32 * (n >> 3) + 8 * (n & 3) + 4 * ((n >> 2) & 1);
+            const int n = lane >> 2, key0 = wave * kWave + 32 * (n >> 3) + 8 * (n & 3) + 4 * ((n >> 2) & 1);
 #pragma unroll
             for (int t = 0; t < 4; ++t)
                 tiles::load_lds16(vres, __umul24(static_cast<uint32_t>(min(key0 + t, N - 1)), row_bytes) + tiles::gather_chunk(lane) + 64 * jj,
                                   0, buf + t * tiles::tile_bytes<32>());
         }
     };
-    if (kBf16 && wave < nchunk) load_values(wave, 0);
+    if (kBf16 && wave < nchunk) load_values(0);
 
     // ---- phase 2: softmax and selection, one wave per query row ----
     {
@@ -284,10 +284,9 @@ __global__ __launch_bounds__(Q * kWave) __attribute__((amdgpu_waves_per_eu(coars
             int32_t* const so = a.sel_idx + ((static_cast<size_t>(b) * a.heads + h) * N + qi) * a.K;
             float* const ko = a.sel_key + ((static_cast<size_t>(b) * a.heads + h) * N + qi) * a.K;
             // Up to kBoundK (less where a lane's keys are alike; N > 64, so every group has a key): the K-th
-            // largest of 64 groups' maxima bounds the
-            // K-th largest key from below, and the few keys at or above it go to LDS (the row's logits are in
-            // registers) in index order, one a lane. The searches then test one value a lane and bit, and the
-            // listing runs once instead of kPerLane times.
+            // largest of 64 groups' maxima bounds the K-th largest key from below, and the few keys at or above
+            // it go to LDS (the row's logits are in registers) in index order, one a lane. The searches then test
+            // one value a lane and bit, and the listing runs once instead of kPerLane times.
             constexpr int kBoundK = bound_max_k<T, D, VA, kPerLane>();
             int nsurv = kWave + 1;
             uint32_t low = 0u;
@@ -374,7 +373,7 @@ __global__ __launch_bounds__(Q * kWave) __attribute__((amdgpu_waves_per_eu(coars
     __syncthreads();
 
     // ---- phase 3: messages m = P V. fp32: on the fp32 MFMA; a wave takes key steps p3_ks, p3_ks + NKS, ... in
-    // batches of kVBatch, two batches in flight. bf16: a wave takes 64 keys at a time; the weights are split
+    // batches of kVBatch, two batches in flight. bf16: a wave takes 64 keys, or none; the weights are split
     // exactly into three bf16 terms as they are read, whose products with the values are exact, so the sums
     // are as accurate as fp32's. ----
     if constexpr (kBf16) {
@@ -385,17 +384,18 @@ __global__ __launch_bounds__(Q * kWave) __attribute__((amdgpu_waves_per_eu(coars
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) acc[ct] = float4_t{0.f, 0.f, 0.f, 0.f};
         const float* prow = Sm + (n16 & (Q - 1)) * pitch;            // P rows past Q repeat (ignored)
-        for (int c = wave; c < nchunk; c += kWaves) {                // uniform
+        static_assert(kPerLane <= kWaves, "a wave has at most one chunk of 64 keys");
+        if (wave < nchunk) {                                         // uniform
 #pragma unroll
             for (int jj = 0; jj < D / 32; ++jj) {
-                if (jj > 0 || c != wave) {
+                if (jj > 0) {
                     wave_lds_sync();                                 // the last rows' reads
-                    load_values(c, jj);
+                    load_values(jj);
                 }
                 wait_lds_loads();
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
-                    const float* pk = prow + c * kWave + 32 * u + 8 * g;
+                    const float* pk = prow + wave * kWave + 32 * u + 8 * g;
                     const float4_t x = *reinterpret_cast<const float4_t*>(pk), y = *reinterpret_cast<const float4_t*>(pk + 4);
                     const Split2 s0 = split2(x[0], x[1]), s1 = split2(x[2], x[3]), s2 = split2(y[0], y[1]), s3 = split2(y[2], y[3]);
                     const bf16x8_t w[3] = {__builtin_bit_cast(bf16x8_t, u32x4_t{s0.hi, s1.hi, s2.hi, s3.hi}),
@@ -444,8 +444,8 @@ __global__ __launch_bounds__(Q * kWave) __attribute__((amdgpu_waves_per_eu(coars
     // The output element of this thread in the epilogue (Q*D <= the Q*64 threads: one each, or none),
     // and for the fused position encoding its operands, requested now that the selection and the
     // message product need their registers no more (held from before the softmax they took d = 64 past the 64
-    // registers that two workgroups of 16 waves leave each other): the 3x3 window of v around the query token (clamped addresses, zero outside the
-    // map through opaque masks), this channel's kernel and its bias.
+    // registers that two workgroups of 16 waves leave each other): the 3x3 window of v around the query token
+    // (clamped addresses, zero outside the map through opaque masks), this channel's kernel and its bias.
     static_assert(D <= kWave, "one output element per thread");
     const int er = static_cast<int>(threadIdx.x) / D, ech = static_cast<int>(threadIdx.x) - er * D;
     const int eqi = tile * Q + er;
@@ -496,25 +496,6 @@ __global__ __launch_bounds__(Q * kWave) __attribute__((amdgpu_waves_per_eu(coars
             store_at<float>(a.msg + map0, (__umul24(static_cast<uint32_t>(qi), static_cast<uint32_t>(C)) + ch) * 4u, s);
         }
     }
-}
-
-// Sum over each aligned group of G consecutive lanes (G = 4, 8 or 16), the same bits in every lane of
-// a group (each step adds two partial sums that the two lanes hold in swapped roles).
-template <int CTRL>
-__device__ __forceinline__ float dpp_f32(float v)
-{
-    return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), CTRL, 0xF, 0xF, false));
-}
-
-template <int G>
-__device__ __forceinline__ float group_sum(float x)
-{
-    static_assert(G == 4 || G == 8 || G == 16, "group of 4, 8 or 16 lanes");
-    x += dpp_f32<kDppXor1>(x);
-    x += dpp_f32<kDppXor2>(x);
-    if constexpr (G >= 8) x += dpp_f32<kDppRowHalfMirror>(x);
-    if constexpr (G >= 16) x += dpp_f32<kDppRowMirror>(x);
-    return x;
 }
 
 // a.lo * b.lo + a.hi * b.hi + c for two packed bf16 pairs, fp32 accumulation

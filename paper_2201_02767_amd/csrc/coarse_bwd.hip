@@ -275,36 +275,37 @@ hipError_t launch_tile(const BwdCoarseArgs& a, hipStream_t stream)
 }
 
 template <typename T, int D, bool VA, int kPerLane>
-hipError_t launch_pass(const BwdCoarseArgs& a, bool keys, hipStream_t stream)
+hipError_t launch_passes(const BwdCoarseArgs& a, hipStream_t stream)
 {
-    return keys ? launch_tile<T, D, VA, kPerLane, true>(a, stream) : launch_tile<T, D, VA, kPerLane, false>(a, stream);
+    const hipError_t e = launch_tile<T, D, VA, kPerLane, false>(a, stream);
+    return e == hipSuccess ? launch_tile<T, D, VA, kPerLane, true>(a, stream) : e;
 }
 
 template <typename T, int D, bool VA>
-hipError_t launch_per_lane(const BwdCoarseArgs& a, bool keys, hipStream_t stream)
+hipError_t launch_per_lane(const BwdCoarseArgs& a, hipStream_t stream)
 {
     switch (bwd_coarse_per_lane(a.N)) {
-    case 1: return launch_pass<T, D, VA, 1>(a, keys, stream);
-    case 2: return launch_pass<T, D, VA, 2>(a, keys, stream);
-    case 3: return launch_pass<T, D, VA, 3>(a, keys, stream);
-    case 4: return launch_pass<T, D, VA, 4>(a, keys, stream);
-    case 5: return launch_pass<T, D, VA, 5>(a, keys, stream);
-    case 6: return launch_pass<T, D, VA, 6>(a, keys, stream);
-    case 8: return launch_pass<T, D, VA, 8>(a, keys, stream);
-    case 12: return launch_pass<T, D, VA, 12>(a, keys, stream);
-    case 16: return launch_pass<T, D, VA, 16>(a, keys, stream);
+    case 1: return launch_passes<T, D, VA, 1>(a, stream);
+    case 2: return launch_passes<T, D, VA, 2>(a, stream);
+    case 3: return launch_passes<T, D, VA, 3>(a, stream);
+    case 4: return launch_passes<T, D, VA, 4>(a, stream);
+    case 5: return launch_passes<T, D, VA, 5>(a, stream);
+    case 6: return launch_passes<T, D, VA, 6>(a, stream);
+    case 8: return launch_passes<T, D, VA, 8>(a, stream);
+    case 12: return launch_passes<T, D, VA, 12>(a, stream);
+    case 16: return launch_passes<T, D, VA, 16>(a, stream);
     }
     return hipErrorInvalidValue;
 }
 
 }  // namespace
 
-hipError_t launch_bwd_coarse(const BwdCoarseArgs& a, int d, bool variant_a, bool use_bf16, bool keys, hipStream_t stream)
+hipError_t launch_bwd_coarse(const BwdCoarseArgs& a, int d, bool variant_a, bool use_bf16, hipStream_t stream)
 {
     if (a.N > QTA_MAX_COARSE) return hipErrorInvalidValue;
 #define QTA_BWD_COARSE_CASE(T, DD)                                                                      \
     if (d == DD)                                                                                        \
-        return variant_a ? launch_per_lane<T, DD, true>(a, keys, stream) : launch_per_lane<T, DD, false>(a, keys, stream);
+        return variant_a ? launch_per_lane<T, DD, true>(a, stream) : launch_per_lane<T, DD, false>(a, stream);
     if (use_bf16) {
         QTA_BWD_COARSE_CASE(bf16, 32)
         QTA_BWD_COARSE_CASE(bf16, 64)

@@ -1021,8 +1021,7 @@ qta_status backward_impl(const void* q, const void* k, const void* v, const floa
     // finished v gradients: those run finest first, below, as do fp32 inputs.)
     if (use_bf16 && !va && !pe && levels > 1 && !only_finest) {
         const BwdCoarseArgs ca = coarse_args();
-        if (launch_bwd_coarse(ca, d, va, use_bf16, false, s) != hipSuccess) return QTA_ERR_HIP;
-        if (launch_bwd_coarse(ca, d, va, use_bf16, true, s) != hipSuccess) return QTA_ERR_HIP;
+        if (launch_bwd_coarse(ca, d, va, use_bf16, s) != hipSuccess) return QTA_ERR_HIP;
         for (int l = c - 1; l >= 0; --l) {
             BwdScanArgs sc;
             BwdLevelArgs a = level_args(l, &sc);
@@ -1073,8 +1072,7 @@ qta_status backward_impl(const void* q, const void* k, const void* v, const floa
     // 3. coarsest level
     {
         const BwdCoarseArgs a = coarse_args();
-        if (launch_bwd_coarse(a, d, va, use_bf16, false, s) != hipSuccess) return QTA_ERR_HIP;
-        if (launch_bwd_coarse(a, d, va, use_bf16, true, s) != hipSuccess) return QTA_ERR_HIP;
+        if (launch_bwd_coarse(a, d, va, use_bf16, s) != hipSuccess) return QTA_ERR_HIP;
     }
     // the position encoding's backward (every level, once all of the level's v gradients are
     // written; before the unpooling, which reads them)

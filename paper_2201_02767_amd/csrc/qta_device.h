@@ -298,34 +298,22 @@ __device__ __forceinline__ int lanes_below(uint64_t mask)
                                      __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
 }
 
-__device__ __forceinline__ float wave_max(float x)
+// Sum over each aligned group of G consecutive lanes (G = 4, 8 or 16), the same bits in every lane of
+// a group (each step adds two partial sums that the two lanes hold in swapped roles).
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float v)
 {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) x = fmaxf(x, __shfl_xor(x, m, kWave));
-    return x;
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), CTRL, 0xF, 0xF, false));
 }
 
-__device__ __forceinline__ float wave_sum(float x)
+template <int G>
+__device__ __forceinline__ float group_sum(float x)
 {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) x += __shfl_xor(x, m, kWave);
-    return x;
-}
-
-__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t x, int m)
-{
-    const uint32_t lo = __shfl_xor(static_cast<uint32_t>(x), m, kWave);
-    const uint32_t hi = __shfl_xor(static_cast<uint32_t>(x >> 32), m, kWave);
-    return (static_cast<uint64_t>(hi) << 32) | lo;
-}
-
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t x)
-{
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-        const uint64_t y = shfl_xor_u64(x, m);
-        x = y > x ? y : x;
-    }
+    static_assert(G == 4 || G == 8 || G == 16, "group of 4, 8 or 16 lanes");
+    x += dpp_f32<kDppXor1>(x);
+    x += dpp_f32<kDppXor2>(x);
+    if constexpr (G >= 8) x += dpp_f32<kDppRowHalfMirror>(x);
+    if constexpr (G >= 16) x += dpp_f32<kDppRowMirror>(x);
     return x;
 }
 
@@ -353,13 +341,6 @@ __device__ __forceinline__ uint64_t rank_word(float score, int32_t idx)
 {
     return (static_cast<uint64_t>(ordered_bits(score)) << 32) | static_cast<uint32_t>(~static_cast<uint32_t>(idx));
 }
-
-__device__ __forceinline__ int32_t rank_word_index(uint64_t w)
-{
-    return static_cast<int32_t>(~static_cast<uint32_t>(w));
-}
-
-__device__ __forceinline__ float rank_word_score(uint64_t w) { return from_ordered_bits(static_cast<uint32_t>(w >> 32)); }
 
 // The keff-th largest of the wave's keys (NPER a lane), built bit by bit from the top on ballots; ends early
 // where the keys at or above the partial cut number exactly keff (the cut is then a lower bound that
@@ -442,44 +423,6 @@ __device__ __forceinline__ void wave_select_top(const uint32_t (&key)[NPER], con
                 open[e] = false;
                 kept[e] = true;
             }
-    }
-}
-
-// Bitonic sort, descending, of NT*64 words held as word[t] in lane l at position t*64 + l.
-template <int NT>
-__device__ __forceinline__ void wave_bitonic_sort_desc(uint64_t (&word)[NT])
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    constexpr int n = NT * kWave;
-#pragma unroll
-    for (int k = 2; k <= n; k <<= 1) {
-#pragma unroll
-        for (int j = k >> 1; j >= 1; j >>= 1) {
-            if (j >= kWave) {
-                const int tj = j / kWave;
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    if (t & tj) continue;
-                    const int e = t * kWave + lane;            // lower element of the pair
-                    const bool desc = (e & k) == 0;
-                    const uint64_t a = word[t], b = word[t | tj];
-                    const bool swap = desc ? (b > a) : (a > b);
-                    word[t] = swap ? b : a;
-                    word[t | tj] = swap ? a : b;
-                }
-            } else {
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const int e = t * kWave + lane;
-                    const uint64_t other = shfl_xor_u64(word[t], j);
-                    const bool lower = (e & j) == 0;
-                    const bool desc = (e & k) == 0;
-                    const bool take_max = (lower == desc);
-                    const bool other_bigger = other > word[t];
-                    word[t] = (take_max == other_bigger) ? other : word[t];
-                }
-            }
-        }
     }
 }
 

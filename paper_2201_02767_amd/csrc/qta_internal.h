@@ -457,8 +457,8 @@ hipError_t launch_bwd_key_bf16(const BwdLevelArgs& a, int d, bool variant_a, boo
 // The counting sort of a level's kept pairs by key, after its query pass; then its key pass.
 hipError_t launch_bwd_sort(const BwdLevelArgs& a, const BwdScanArgs& sc, bool use_bf16, hipStream_t stream);
 hipError_t launch_bwd_keys(const BwdLevelArgs& a, int d, bool variant_a, bool use_bf16, bool finest, hipStream_t stream);
-// keys: the key pass (after the query pass of the same level), else the query pass.
-hipError_t launch_bwd_coarse(const BwdCoarseArgs& a, int d, bool variant_a, bool use_bf16, bool keys, hipStream_t stream);
+// The query pass, then the key pass.
+hipError_t launch_bwd_coarse(const BwdCoarseArgs& a, int d, bool variant_a, bool use_bf16, hipStream_t stream);
 hipError_t launch_bwd_unpool(const BwdUnpoolArgs& a, hipStream_t stream);
 
 }  // namespace qta
