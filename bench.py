@@ -36,9 +36,11 @@ COARSE_MFMA_TARGET = 0.40
 PROFILES = os.path.join(ROOT, "profiles")
 _CSRC = os.path.join(ROOT, "paper_2201_02767_amd", "csrc")
 # every source compiled into the roofline kernel: its counters are stale once one of them changes
-FINE_SRC = [os.path.join(_CSRC, f) for f in ("fine.hip", "fine_item.h", "qta_device.h", "qta_internal.h")]
-BWD_SRC = [os.path.join(_CSRC, f) for f in ("backward.hip", "qta_device.h", "qta_internal.h")]
-COARSE_SRC = [os.path.join(_CSRC, f) for f in ("coarse.hip", "qta_device.h", "qta_internal.h")]
+FINE_SRC = [os.path.join(_CSRC, f) for f in ("fine.hip", "fine_item.h", "fine_bf16.h", "bf16_tiles.h", "qta_device.h",
+                                             "qta_internal.h")]
+BWD_SRC = [os.path.join(_CSRC, f) for f in ("backward.hip", "backward_bf16.hip", "bwd_bf16.h", "bf16_tiles.h",
+                                            "qta_device.h", "qta_internal.h")]
+COARSE_SRC = [os.path.join(_CSRC, f) for f in ("coarse.hip", "bf16_tiles.h", "qta_device.h", "qta_internal.h")]
 
 
 def log(msg: str) -> None:
@@ -366,7 +368,8 @@ def main() -> int:
         traffic = measured_traffic(wl.name, "bwd_level_finest", BWD_SRC)
         roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                "kernel": "finest-level backward step (query pass, counting sort, key pass; 6 launches)",
+                "kernel": "finest-level backward step (" + ("combine pass, " if wl.dtype == "bf16" else "")
+                          + "query pass, counting sort, key pass and its reduction)",
                 "kernel_us": round(k_us, 3),
                 "algorithmic_bytes": algo}
         log(f"bench: finest-level backward step {k_us:.2f} us/launch, {algo / 1e6:.1f} MB algorithmic -> "
@@ -379,7 +382,11 @@ def main() -> int:
         traffic = measured_traffic(wl.name)
         roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                "kernel": "fine_attn_kernel (finest level, fused combine)", "kernel_us": round(k_us, 3),
+                "kernel": ("fine_bf16_kernel" if wl.dtype == "bf16" else "fine_attn_kernel")
+                          + " (finest level, fused combine"
+                          + (", without the position encoding: the layer's own finest level is fine_attn_kernel with it)"
+                             if wl.pe else ")"),
+                "kernel_us": round(k_us, 3),
                 "algorithmic_bytes": algo}
         if traffic:
             # the same launch time against the bytes the counters saw cross the L2 (HBM or MALL)
