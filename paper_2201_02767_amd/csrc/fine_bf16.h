@@ -28,9 +28,9 @@
 // cost 19 (rows in the L1) to 39 (64-byte rows from the L2, whose lines are 128 bytes). It also moved the
 // values through 2-byte LDS writes, worked out every slot's address in four lanes, loaded w and the ancestors
 // lane by lane (64 * 4 scattered words for w alone, 16 of its 77 us) and stored 2 bytes a lane. VALU
-// instructions a wave 400 -> 216, LDS 52 -> 19; 200x336 maps, 2 heads x 32, K = 16: 76.5 -> 51.6 us;
-// 120x160, 8 x 32, K = 8: 52.4 -> 40.9; 200x334, 1 x 32, K = 32: 44.8 -> 33.2; 32 maps of 56x56, 1 x 64,
-// K = 8: 29.5 -> 17.0.
+// instructions a wave 400 -> 171, LDS 52 -> 19. One launch among others like it: 200x336 maps, 2 heads x 32,
+// K = 16, batch 2: 77.0 -> 50.7 us; 120x160, 8 x 32, K = 8, batch 2: 53.0 -> 42.3; 200x334, 1 x 32, K = 32, batch 2:
+// 45.1 -> 30.8; 32 maps of 56x56, 1 x 64, K = 8: 29.8 -> 16.0. In a whole layer they take 1 to 4 us more.
 #ifndef QTA_FINE_BF16_H
 #define QTA_FINE_BF16_H
 

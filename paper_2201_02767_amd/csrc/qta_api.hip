@@ -73,7 +73,9 @@ qta_status check_k_levels(const int* Kl, int levels)
 
 // Intermediate level l (produced by the pyramid, gathered by level l's attention) is stored
 // parent-blocked when V comes from the pyramid. The input level stays NHWC: a blocked copy of it
-// would cost a write and a read of k and v for no gain in the gathers.
+// costs a write of k and v, and the gathers that take a row per lane (fp32) cost the same wherever the
+// rows lie, so it lost there. The bf16 kernels' gathers, a quad per row, are cheaper where two rows
+// share a 128-byte line, as a blocked copy would have them with d = 32; that has not been measured.
 bool use_blocked(const int* Kl, int l, int levels, bool v_supplied)
 {
     (void)Kl;

@@ -14,11 +14,11 @@
 //   4. at most 64 survivors, one a lane: each counts the words (score, inverted name) above its own and,
 //      when fewer than K are, writes itself to that place. So the order is (score descending, name
 //      ascending), and repeated names stay separate candidates.
-// What bounds it: for long rows their read (9600 rows of 1200, K = 16: 14.4 us, 3.3 of the 5.1 TB/s a copy
-// reaches), for short ones instruction issue. Rows of one score throughout, us a call (the host takes 10): 1e4 rows
-// of 100, K = 4 10 and K = 33 15; 5e3 of 200, K = 16 10; 244 of 4096, K = 4 10, with drawn names 22. With one
-// wave-wide 64-bit minimum for each place at the cut they took 24, 57, 22, 43 and 44; with K rounds of a maximum over
-// the whole row 10, 53, 17, 22 and 22 (and the long rows 226).
+// What its time goes to: for long rows mostly their read (9600 rows of 1200, K = 16: 14.4 us, 3.3 TB/s or 65% of
+// the rate of a copy), for short ones instruction issue. Rows of one score throughout, us a call (the host takes
+// 10): 1e4 rows of 100, K = 4 10 and K = 33 15; 5e3 of 200, K = 16 10; 244 of 4096, K = 4 10, with drawn names 22.
+// With one wave-wide 64-bit minimum for each place at the cut they took 24, 57, 22, 43 and 44; with K rounds of a
+// maximum over the whole row 10, 53, 17, 22 and 22 (and the long rows 226).
 #include "qta_device.h"
 #include "qta_internal.h"
 
