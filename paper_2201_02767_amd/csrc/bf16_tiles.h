@@ -2,8 +2,8 @@
 //
 // A wave works on slots in NT tiles of 16 (NT = 1, 2, 4, 8 or 16), each slot a row of D channels somewhere in
 // a map. Rows come in by gathers in which lanes 4n .. 4n+3 take the four 16-byte chunks (per 64 bytes) of
-// tile row n, lane l chunk (l & 3) ^ (n >> 2): four neighbouring lanes on one row cost the L1 19 to 39 cycles
-// an instruction, a lane per row 46. They land in LDS (straight from memory, or from registers) in lane
+// tile row n, lane l chunk (l & 3) ^ (n >> 2): four neighbouring lanes on one row cost a CU 19 (L1) to 39 (L2)
+// cycles an instruction, a lane per row 46 to 64. They land in LDS (straight from memory, or from registers) in lane
 // order, as [tile][D / 32][16 rows][4 places] chunks, place p of row n holding chunk p ^ (n >> 2). From there
 //   - tile_operand reads MFMA operand lanes (16g + n: chunk g of row n) without bank conflicts,
 //   - mma_rows contracts over the slots: weights [4 vectors][16][NT] times the rows, read transposed.

@@ -6,8 +6,8 @@
 // split exactly into three bf16 terms (8 + 8 + 8 bits), whose products with a bf16 row are exact in the
 // MFMA's fp32 accumulator, so the sums are as accurate as on the fp32 MFMA at a sixth of its time.
 //
-// What bounds them, before -> now: the previous forms gathered with a lane per row (46 cycles of the L1 an
-// instruction, see bf16_tiles.h) and read the rows back from LDS two bytes at a time, one fp32 4x4 MFMA per
+// What bounds them, before -> now: the previous forms gathered with a lane per row (46 to 64 cycles of a CU
+// an instruction, see bf16_tiles.h) and read the rows back from LDS two bytes at a time, one fp32 4x4 MFMA per
 // slot. Finest level in a training step, 200x336 maps, 2 x 32 channels, K = 16, batch 2: query pass 125 us with
 // the combination's backward -> 69 and 22 for that, key pass with its reduction 172 -> 111; 32 maps of 56x56,
 // 1 x 64, K = 8: query pass 50 -> 25 and 14, key pass 76 -> 45.

@@ -24,8 +24,9 @@
 //
 // What bounds it, and what was measured (the finest level, before -> now): the L1's line rate in the gathers,
 // then the fixed work per wave. The previous form gathered with a lane per row (lane 16g + n: chunk g of row
-// n), which costs the L1 46 cycles per instruction wherever the rows lie; four neighbouring lanes on one row
-// cost 19 (rows in the L1) to 39 (64-byte rows from the L2, whose lines are 128 bytes). It also moved the
+// n). Cycles of a CU an instruction of 16 64-byte rows, a lane per row against four neighbouring lanes on one: from
+// the L1 46 and 19; from the L2, whose lines are 128 bytes, one row a line 64 and 38 to 39, runs of four rows side by
+// side 34 and 21; past the L2, one row a line, 155 to 165 either way, such runs 78. It also moved the
 // values through 2-byte LDS writes, worked out every slot's address in four lanes, loaded w and the ancestors
 // lane by lane (64 * 4 scattered words for w alone, 16 of its 77 us) and stored 2 bytes a lane. VALU
 // instructions a wave 400 -> 171, LDS 52 -> 19. One launch among others like it: 200x336 maps, 2 heads x 32,
