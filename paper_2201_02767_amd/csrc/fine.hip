@@ -56,8 +56,8 @@ hipError_t launch_one(const FineArgs& a, hipStream_t stream)
     return hipGetLastError();
 }
 
-// The bf16 form (fine_bf16.h), NT tiles of 16 candidate slots.
-template <int D, int NT, bool VA, bool FINEST, bool ROW>
+// The bf16 form (fine_bf16.h), NT tiles of 16 candidate slots, the first LIVE of them gathered.
+template <int D, int NT, int LIVE, bool VA, bool FINEST, bool ROW>
 __global__ __launch_bounds__(256) void fine_bf16_kernel(FineArgs a)
 {
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
@@ -67,10 +67,10 @@ __global__ __launch_bounds__(256) void fine_bf16_kernel(FineArgs a)
     const int it = xcd_remap(blockIdx.x, gridDim.x) * wpb + wave;
     if (it >= nitems) return;              // whole wave leaves; only wave-level syncs follow
     extern __shared__ __align__(16) unsigned char smem[];
-    fine16::item<D, NT, VA, FINEST, ROW>(a, it, smem + wave * fine16::wave_bytes<D, NT>());
+    fine16::item<D, NT, LIVE, VA, FINEST, ROW>(a, it, smem + wave * fine16::wave_bytes<D, NT>());
 }
 
-template <int D, int NT, bool VA, bool FINEST, bool ROW>
+template <int D, int NT, bool VA, bool FINEST, bool ROW, int LIVE = NT>
 hipError_t launch_bf16(const FineArgs& a, hipStream_t stream)
 {
     constexpr size_t wave_bytes = fine16::wave_bytes<D, NT>();
@@ -78,14 +78,14 @@ hipError_t launch_bf16(const FineArgs& a, hipStream_t stream)
     while (wpb > 1 && wpb * wave_bytes > device_max_lds()) --wpb;
     if (wave_bytes > device_max_lds()) return hipErrorInvalidValue;
     static std::atomic<unsigned long long> configured{0};     // devices whose LDS limit is raised
-    if (hipError_t e = set_max_lds_once(reinterpret_cast<const void*>(&fine_bf16_kernel<D, NT, VA, FINEST, ROW>), configured);
+    if (hipError_t e = set_max_lds_once(reinterpret_cast<const void*>(&fine_bf16_kernel<D, NT, LIVE, VA, FINEST, ROW>), configured);
         e != hipSuccess)
         return e;
     const long long np = static_cast<long long>(a.Hp) * a.Wp;
     const long long items = static_cast<long long>(a.B) * a.heads * (ROW ? (np + 1) / 2 : np);
     const long long blocks = (items + wpb - 1) / wpb;
     if (blocks * wpb >= 0x7FFFFFFFLL) return hipErrorInvalidValue;     // work items are int
-    hipLaunchKernelGGL((fine_bf16_kernel<D, NT, VA, FINEST, ROW>), dim3(static_cast<unsigned>(blocks)),
+    hipLaunchKernelGGL((fine_bf16_kernel<D, NT, LIVE, VA, FINEST, ROW>), dim3(static_cast<unsigned>(blocks)),
                        dim3(wpb * kWave), wpb * wave_bytes, stream, a);
     return hipGetLastError();
 }
@@ -97,7 +97,15 @@ hipError_t launch_bf16_tiles(const FineArgs& a, hipStream_t stream)
     if (nslot <= 16) return launch_bf16<D, 1, VA, FINEST, ROW>(a, stream);
     if (nslot <= 32) return launch_bf16<D, 2, VA, FINEST, ROW>(a, stream);
     if (nslot <= 64) return launch_bf16<D, 4, VA, FINEST, ROW>(a, stream);
+    // Tiles are a power of two; past the last one with a slot they would be gathered for nothing, and the general
+    // kernel, which stopped there, was ahead: 121x164 maps, batch 4, 4 levels, us a layer, general, all tiles, these:
+    // A, 2 x 64, K = 17 155.6, 164, 155; 2 x 32, K = 33 183, 195, 182, B 189, 197, 181; K = 48 258, 206, 191, B 264,
+    // 210, 189. With K = 17 to 24 only A with d = 64 had fallen behind; the others were 6 to 15% ahead with all eight.
+    if constexpr (VA && D == 64) {
+        if (nslot <= 96) return launch_bf16<D, 8, VA, FINEST, ROW, 6>(a, stream);
+    }
     if (nslot <= 128) return launch_bf16<D, 8, VA, FINEST, ROW>(a, stream);
+    if (nslot <= 192) return launch_bf16<D, 16, VA, FINEST, ROW, 12>(a, stream);
     if (nslot <= 256) return launch_bf16<D, 16, VA, FINEST, ROW>(a, stream);
     return hipErrorInvalidValue;
 }

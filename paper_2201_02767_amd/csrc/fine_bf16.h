@@ -48,7 +48,8 @@ using namespace tiles;
 template <int D, int NT>
 constexpr int wave_bytes() { return NT * tile_bytes<D>() + (NT > 8 ? 128 * NT : 1024); }
 
-template <int D, int NT, bool VA, bool FINEST, bool ROW>
+// LIVE: the tiles that can hold a slot; those after them are not gathered (zeros in LDS, masked logits).
+template <int D, int NT, int LIVE, bool VA, bool FINEST, bool ROW>
 __device__ __forceinline__ void item(const FineArgs& a, const int it, unsigned char* const base)
 {
     constexpr int RB = D * 2;                        // bytes of one head's row
@@ -165,19 +166,17 @@ __device__ __forceinline__ void item(const FineArgs& a, const int it, unsigned c
 #pragma unroll
         for (int i = 0; i < kTB; ++i)
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) kc[i][j] = load_at<uint4>(kg, off[t0 + i] + 64 * j);
+            for (int j = 0; j < NJ; ++j)
+                if (t0 + i < LIVE) kc[i][j] = load_at<uint4>(kg, off[t0 + i] + 64 * j);
     };
     load_keys(0);
     const __amdgpu_buffer_rsrc_t vres = map_resource(vg);
-    // value rows into LDS: one instruction lands its lanes' chunks in lane order. The last quarter of 16 tiles holds no
-    // slot up to K = 48; QuadTree-A leaves it out (zeros): 160x224 maps, 2 x 32, K = 36 120 -> 115 us (the general
-    // kernel, nine tiles of 16: 116), K = 64 133 -> 131; B would gain 3% there and lose 2% at K = 64
-    auto tile_live = [&](int t) { return !VA || NT < 16 || t < 12 || nslot > 192; };       // uniform
+    // value rows into LDS: one instruction lands its lanes' chunks in lane order
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
-            if (tile_live(t)) load_lds16(vres, off[t], 64 * j, vlds + t * TS + j * 1024);
+            if (t < LIVE) load_lds16(vres, off[t], 64 * j, vlds + t * TS + j * 1024);
             else *(lds_ptr<u32x4_t>)(vlds + t * TS + j * 1024 + lane * 16) = u32x4_t{0u, 0u, 0u, 0u};
         }
 
@@ -231,14 +230,13 @@ __device__ __forceinline__ void item(const FineArgs& a, const int it, unsigned c
     float xt[NT];
 #pragma unroll
     for (int t0 = 0; t0 < NT; t0 += kTB) {
-        if (!tile_live(t0)) {                                    // uniform
-#pragma unroll
-            for (int i = 0; i < kTB; ++i) xt[t0 + i] = 0.f;      // (masked below)
-            continue;
-        }
         if (t0 > 0) load_keys(t0);
 #pragma unroll
         for (int i = 0; i < kTB; ++i) {
+            if (t0 + i >= LIVE) {
+                xt[t0 + i] = 0.f;                                // (masked below)
+                continue;
+            }
             float4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int j = 0; j < NJ; ++j)

@@ -362,6 +362,9 @@ def test_forward_parity(dev, variant, dtype, B, H, W, heads, d, L, K):
     (1, 19, 22, 2, 32, 3, 5, False),       # two tiles, the second partly live
     (1, 21, 26, 3, 64, 3, 9, False),       # four tiles, d = 64
     (1, 33, 31, 2, 32, 6, 17, False),      # eight tiles; five ancestors (two groups), odd at every level
+    (1, 27, 29, 1, 64, 3, 24, False),      # eight tiles, d = 64, the last two without a slot
+    (1, 29, 27, 1, 64, 3, 25, False),      # and with one
+    (2, 2, 61, 1, 64, 5, 24, True),        # the same on one-row maps
     (1, 22, 25, 1, 64, 3, 33, False),      # sixteen tiles, d = 64
     (1, 35, 31, 1, 32, 3, 48, False),      # sixteen tiles, the last four without a slot
     (1, 31, 35, 1, 32, 3, 49, False),      # and with one
